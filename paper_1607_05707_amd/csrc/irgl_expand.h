@@ -68,26 +68,48 @@ __device__ __forceinline__ void op_range<SsspOp>(const SsspOp &op, const int32_t
     }
 }
 
-// Pop-time decision for vertex v with value val (default: expand it).
+// Pop vertex v: its value, the row range [r0, r1) to relax (empty when it is
+// not expanded) and whether it is expanded (ex) and listed for the heavy
+// pass (hp).  Everything read depends on v alone and is read at once.
+template <class Op>
+__device__ __forceinline__ void pop_vertex(const Op &op, const int32_t *__restrict__ rp, int v, uint32_t &val,
+                                           int &r0, int &r1, bool &, bool &ex) {
+    if constexpr (Op::kPush) {  // a worklist: expanded whatever its value
+        val = op.vertex_value(v);
+        r0 = rp[v];
+        r1 = rp[v + 1];
+        ex = true;
+    } else {  // all vertices: few of them may be active
+        val = op.vertex_value(v);
+        if (op.active(val)) {
+            r0 = rp[v];
+            r1 = rp[v + 1];
+            ex = true;
+        }
+    }
+}
 // SSSP: a vertex whose distance has not changed since its last expansion is
 // not expanded again (every edge was relaxed with this distance, or a
 // smaller one no longer current is impossible: distances only fall); an
-// expanded vertex is listed once per bucket for the heavy pass (*hpush).
-template <class Op>
-__device__ __forceinline__ bool op_pop(const Op &, int, uint32_t, bool &) {
-    return true;
-}
+// expanded vertex is listed once per bucket for the heavy pass.
 template <>
-__device__ __forceinline__ bool op_pop<SsspOp>(const SsspOp &op, int v, uint32_t val, bool &hpush) {
-    if (op.expd) {
-        if (op.expd[v] == val) return false;
-        op.expd[v] = val;
+__device__ __forceinline__ void pop_vertex<SsspOp>(const SsspOp &op, const int32_t *__restrict__ rp, int v,
+                                                   uint32_t &val, int &r0, int &r1, bool &hp, bool &ex) {
+    val = op.dist[v];
+    r0 = op.split && op.heavy ? op.split[v] : rp[v];
+    r1 = op.split && !op.heavy ? op.split[v] : rp[v + 1];
+    const uint32_t last = op.expd ? op.expd[v] : ~val;
+    const uint32_t hst = op.hstamp ? op.hstamp[v] : op.bucket;
+    if (op.expd && last == val) {
+        r1 = r0;
+        return;
     }
-    if (op.hstamp && op.hstamp[v] != op.bucket) {
+    if (op.expd) op.expd[v] = val;
+    if (hst != op.bucket) {
         op.hstamp[v] = op.bucket;
-        hpush = true;
+        hp = true;
     }
-    return true;
+    ex = true;
 }
 
 // Heavy out-degree of vertex v (the part of its row a heavy pass scans).
@@ -151,26 +173,48 @@ __device__ __forceinline__ void drain_all(Pushers &pu, S &sm) {
 }
 
 // Relax U edges of one lane and push the survivors (all 64 lanes call it).
+// e[k] is a valid entry of the graph also where act[k] is false, so the
+// column and weight loads need no branch of their own.
 template <class Op>
 __device__ __forceinline__ void relax_and_push(const Op &op, const int32_t *__restrict__ col,
                                                const int (&e)[Op::kU], bool (&act)[Op::kU], const int (&sv)[Op::kU],
                                                const uint32_t (&sval)[Op::kU], Pushers &pu) {
     int d[Op::kU];
+    uint32_t ew[Op::kU];
     bool far[Op::kU];
+    bool any = false;
+#pragma unroll
+    for (int k = 0; k < Op::kU; ++k) any |= act[k];
+    if (__ballot(any) == 0ull) return;  // uniform across the wavefront
 #pragma unroll
     for (int k = 0; k < Op::kU; ++k) {
-        d[k] = act[k] ? col[e[k]] : 0;
+        d[k] = col[e[k]];
+        ew[k] = op.edge_value(e[k]);
         far[k] = false;
     }
-    op.relax(e, d, sv, sval, act, far, pu.fmin, pu.tries, pu.wins);
+    phase(d);
+    op.relax(ew, d, sv, sval, act, far, pu.fmin, pu.tries, pu.wins);
+    // out-degrees of the pushed vertices: read while they are being queued
+    uint32_t lo[Op::kU], hi[Op::kU];
     if (!Op::kFar && pu.deg_rp) {
 #pragma unroll
-        for (int k = 0; k < Op::kU; ++k)
-            if (act[k]) pu.mf += static_cast<unsigned long long>(pu.deg_rp[d[k] + 1] - pu.deg_rp[d[k]]);
+        for (int k = 0; k < Op::kU; ++k) {
+            lo[k] = hi[k] = 0u;
+            if (act[k]) {
+                lo[k] = static_cast<uint32_t>(pu.deg_rp[d[k]]);
+                hi[k] = static_cast<uint32_t>(pu.deg_rp[d[k] + 1]);
+            }
+        }
     }
     if (Op::kPush) {
 #pragma unroll
         for (int k = 0; k < Op::kU; ++k) pu.near(act[k], d[k]);
+    }
+    if (!Op::kFar && pu.deg_rp) {
+        phase(lo);
+        phase(hi);
+#pragma unroll
+        for (int k = 0; k < Op::kU; ++k) pu.mf += static_cast<unsigned long long>(hi[k] - lo[k]);
     }
     if (Op::kFar) {
 #pragma unroll
@@ -199,6 +243,7 @@ __device__ __forceinline__ void stride_range(const Op &op, const int32_t *__rest
         for (int k = 0; k < Op::kU; ++k) {
             e[k] = e0 + k * width + li;
             act[k] = e[k] < r1;
+            e[k] = min(e[k], r1 - 1);
         }
         relax_and_push(op, col, e, act, svs, svals, pu);
     }
@@ -252,12 +297,8 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
             if (lane == 0) set_error(pu.sk.ctrl, kErrInternal, false);
             return;
         }
-        val = op.vertex_value(v);
         bool hp = false, ex = false;
-        if (op.active(val) && op_pop(op, v, val, hp)) {
-            op_range(op, row_ptr, v, r0, r1);
-            ex = true;
-        }
+        pop_vertex(op, row_ptr, v, val, r0, r1, hp, ex);
         pu.heavy(hp && lane == 0, v);
         if (hp && lane == 0) pu.hdeg += op_heavy_degree(op, row_ptr, v);
         if (ex) pu.hminv = min(pu.hminv, val);  // every expansion, listed or not
@@ -296,25 +337,28 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
     const uint32_t tsz = (Op::kFar && cnt_in < stride)
                              ? min(static_cast<uint32_t>(B), max(128u, (cnt_in + tm.size - 1) / tm.size))
                              : static_cast<uint32_t>(B);
+    // The next tile is reserved while this one's rows are looked up, and its
+    // items are read before this one's edges are relaxed.
     uint32_t tile = tm.id;
+    const auto item = [&](uint32_t t) -> int {
+        const uint32_t i = t * tsz + static_cast<uint32_t>(tid);
+        if (static_cast<uint32_t>(tid) >= tsz || t * tsz >= cnt_in || i >= cnt_in) return -1;
+        return in ? in[i] : static_cast<int>(i);
+    };
+    int v = item(tile);
     for (;;) {
-        const uint32_t base = tile * tsz;
-        if (base >= cnt_in) break;  // uniform across the workgroup
-        const uint32_t i = base + tid;
-        int v = -1, r0 = 0, r1 = 0;
+        if (tile * tsz >= cnt_in) break;  // uniform across the workgroup
+        uint32_t next_tile = tile + tm.size;
+        if (tile_ctr && tid == 0) next_tile = tm.size + atomicAdd(tile_ctr, 1u);
+        int r0 = 0, r1 = 0;
         uint32_t val = 0;
         bool hp = false, ex = false;
-        if (static_cast<uint32_t>(tid) < tsz && i < cnt_in) {
-            v = in ? in[i] : static_cast<int>(i);
+        if (static_cast<uint32_t>(tid) < tsz && tile * tsz + static_cast<uint32_t>(tid) < cnt_in) {
             if (static_cast<uint32_t>(v) >= n) {  // never expected: a corrupt worklist entry
                 set_error(pu.sk.ctrl, kErrInternal, false);
                 v = -1;
             } else {
-                val = op.vertex_value(v);
-                if (op.active(val) && op_pop(op, v, val, hp)) {
-                    op_range(op, row_ptr, v, r0, r1);
-                    ex = true;
-                }
+                pop_vertex(op, row_ptr, v, val, r0, r1, hp, ex);
             }
         }
         pu.heavy(hp, v);
@@ -385,6 +429,7 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
         // workgroup needs ceil(total / (B*U)) rounds whatever the degree mix.
         const int incl = wave_inclusive_scan(deg);
         if (lane == kWave - 1) sm.wsum[wid] = incl;
+        if (tid == 0) sm.tile = next_tile;
         __syncthreads();
         int total = 0, wpre = 0;
 #pragma unroll
@@ -397,6 +442,8 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
         sm.gr0[tid] = r0;
         sm.vtx[tid] = v;
         sm.vval[tid] = val;
+        tile = sm.tile;
+        v = item(tile);
         __syncthreads();
         for (int done = 0; done < total; done += kChunk) {
             int e[Op::kU], sv[Op::kU];
@@ -416,11 +463,7 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
             }
             relax_and_push(op, col, e, act, sv, sval, pu);
         }
-        if (tile_ctr) {
-            if (tid == 0) sm.tile = tm.size + atomicAdd(tile_ctr, 1u);
-        }
-        __syncthreads();  // the scan arrays are rewritten by the next tile; sm.tile is set
-        tile = tile_ctr ? sm.tile : tile + tm.size;
+        __syncthreads();  // the scan arrays are rewritten by the next tile
     }
 }
 

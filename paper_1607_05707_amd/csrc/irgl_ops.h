@@ -116,10 +116,13 @@ struct Params {
 };
 
 // ---------------------------------------------------------------------------
-// Relax operators.  relax(e, d, sv, sval, act) receives U scanned edges
-// e[k] = (sv[k] -> d[k]) of this lane, act[k] marking the live ones, and
-// leaves act[k] true for each destination that must be pushed.  `tries` /
-// `wins` count this lane's claim atomics and the successful ones.
+// Relax operators.  relax(ew, d, sv, sval, act) receives U scanned edges
+// sv[k] -> d[k] of this lane with the values ew[k] that edge_value() read for
+// them (weights), act[k] marking the live ones (d[k] is a valid vertex also
+// for the others), and leaves act[k] true for each destination that must be
+// pushed.  `tries` / `wins` count this lane's claim atomics and the
+// successful ones.  Each step issues its U accesses before it uses any
+// (phase()).
 // ---------------------------------------------------------------------------
 struct BfsOp {
     static constexpr bool kPush = true;
@@ -135,7 +138,8 @@ struct BfsOp {
     const int32_t *perm;      // relabelled graph: parents are stored as caller ids
     __device__ __forceinline__ uint32_t vertex_value(int) const { return 0u; }
     __device__ __forceinline__ bool active(uint32_t) const { return true; }
-    __device__ __forceinline__ void relax(const int (&)[kU], const int (&d)[kU], const int (&sv)[kU],
+    __device__ __forceinline__ uint32_t edge_value(int) const { return 0u; }
+    __device__ __forceinline__ void relax(const uint32_t (&)[kU], const int (&d)[kU], const int (&sv)[kU],
                                           const uint32_t (&)[kU], bool (&act)[kU], bool (&)[kU],
                                           uint32_t &, uint32_t &tries, uint32_t &wins) const {
         // Cheapest filter first: the n/8-byte bitmap stays resident in L2.
@@ -143,7 +147,8 @@ struct BfsOp {
         if (visited) {
             uint32_t wd[kU];
 #pragma unroll
-            for (int k = 0; k < kU; ++k) wd[k] = act[k] ? visited[static_cast<uint32_t>(d[k]) >> 5] : 0u;
+            for (int k = 0; k < kU; ++k) wd[k] = visited[static_cast<uint32_t>(d[k]) >> 5];
+            phase(wd);
 #pragma unroll
             for (int k = 0; k < kU; ++k) act[k] = act[k] && !(wd[k] & (1u << (d[k] & 31)));
         }
@@ -152,11 +157,19 @@ struct BfsOp {
         uint32_t lv[kU];
 #pragma unroll
         for (int k = 0; k < kU; ++k) lv[k] = act[k] ? level[d[k]] : 0u;
+        phase(lv);
+        uint32_t old[kU];
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
             act[k] = act[k] && lv[k] == kInf;
             tries += act[k] ? 1u : 0u;
-            if (act[k]) act[k] = atomicCAS(&level[d[k]], kInf, next) == kInf;
+            old[k] = no_value();
+            if (act[k]) old[k] = atomicCAS(&level[d[k]], kInf, next);
+        }
+        phase(old);
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            act[k] = act[k] && old[k] == kInf;
             wins += act[k] ? 1u : 0u;
         }
         if (parent) {
@@ -229,65 +242,83 @@ struct SsspOp {
     uint32_t heavy = 0;          // 1: this invocation relaxes heavy ranges
     __device__ __forceinline__ uint32_t vertex_value(int v) const { return dist[v]; }
     __device__ __forceinline__ bool active(uint32_t) const { return true; }
-    __device__ __forceinline__ void relax(const int (&e)[kU], const int (&d)[kU], const int (&)[kU],
+    __device__ __forceinline__ uint32_t edge_value(int e) const { return w[e]; }
+    __device__ __forceinline__ void relax(const uint32_t (&ew)[kU], const int (&d)[kU], const int (&)[kU],
                                           const uint32_t (&dv)[kU], bool (&act)[kU],
                                           bool (&far)[kU], uint32_t &fmin, uint32_t &tries, uint32_t &wins) const {
-        uint32_t nd[kU], cur[kU];
+        uint32_t nd[kU], cur[kU], old[kU], was[kU];
         // a settled destination cannot improve (weights >= 1): skip it with an
         // L2-resident bit test instead of a probe of dist[]
         if (settled) {
 #pragma unroll
-            for (int k = 0; k < kU; ++k) cur[k] = act[k] ? settled[static_cast<uint32_t>(d[k]) >> 5] : 0u;
+            for (int k = 0; k < kU; ++k) cur[k] = settled[static_cast<uint32_t>(d[k]) >> 5];
+            phase(cur);
 #pragma unroll
             for (int k = 0; k < kU; ++k) act[k] = act[k] && !(cur[k] & (1u << (d[k] & 31)));
         }
-#pragma unroll
-        for (int k = 0; k < kU; ++k) nd[k] = act[k] ? w[e[k]] : 0u;
         bool ovf = false;
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
-            const uint32_t s = dv[k] + nd[k];
+            const uint32_t s = dv[k] + ew[k];
             const bool bad = act[k] && (s < dv[k] || s == kInf);  // does not fit below INF
             ovf |= bad;
             act[k] = act[k] && !bad;
             nd[k] = s;
         }
         if (ovf) set_error(ctrl, kErrOverflow, false);
+        if (shadow16) {  // uniform
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
-            if (shadow16) {  // uniform
-                const uint32_t h = act[k] ? reinterpret_cast<const uint16_t *>(shadow)[d[k]] : 0u;
-                cur[k] = h == 0xFFFFu ? kInf : h;
-            } else {
-                cur[k] = act[k] ? shadow[d[k]] : 0u;
-            }
+            for (int k = 0; k < kU; ++k)
+                cur[k] = act[k] ? reinterpret_cast<const uint16_t *>(shadow)[d[k]] : 0u;
+            phase(cur);
+#pragma unroll
+            for (int k = 0; k < kU; ++k) cur[k] = cur[k] == 0xFFFFu ? kInf : cur[k];
+        } else {
+#pragma unroll
+            for (int k = 0; k < kU; ++k) cur[k] = act[k] ? shadow[d[k]] : 0u;
+            phase(cur);
         }
+        // The claim, and with it a probe of the word that says whether d is
+        // listed already: d goes to the next worklist (near, at most once per
+        // invocation by the push stamp) or to the far list (at most once
+        // while listed).  A probe may be older than the claim: a set mark
+        // stays set until the list is read, after a barrier.
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
             act[k] = act[k] && nd[k] < cur[k];
             tries += act[k] ? 1u : 0u;
-            if (act[k]) act[k] = nd[k] < atomicMin(&dist[d[k]], nd[k]);
-            wins += act[k] ? 1u : 0u;
-            if (act[k]) {
+            far[k] = act[k] && nd[k] >= thresh;
+            old[k] = no_value();
+            if (act[k]) old[k] = atomicMin(&dist[d[k]], nd[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            cur[k] = no_value();
+            if (act[k]) cur[k] = (far[k] ? far_flag : stamp)[d[k]];
+        }
+        phase(cur);
+        phase(old);
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            const bool won = act[k] && nd[k] < old[k];
+            wins += won ? 1u : 0u;
+            if (won) {
                 if (shadow16) reinterpret_cast<uint16_t *>(shadow)[d[k]] = static_cast<uint16_t>(min(nd[k], 0xFFFFu));
                 else shadow[d[k]] = nd[k];
             }
-        }
-#pragma unroll
-        for (int k = 0; k < kU; ++k) {
-            far[k] = act[k] && nd[k] >= thresh;
-            act[k] = act[k] && nd[k] < thresh;
+            far[k] = won && far[k];
+            act[k] = won && !far[k] && cur[k] != it;
             if (far[k]) fmin = min(fmin, nd[k]);  // lower bound of the far list
+            far[k] = far[k] && cur[k] == 0u;
+            was[k] = no_value();
+            if (act[k]) was[k] = atomicExch(&stamp[d[k]], it);
+            if (far[k]) was[k] = atomicExch(&far_flag[d[k]], 1u);
         }
-        // near: push d at most once per invocation; far: at most once while listed
-#pragma unroll
-        for (int k = 0; k < kU; ++k) cur[k] = act[k] ? stamp[d[k]] : (far[k] ? far_flag[d[k]] : it);
+        phase(was);
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
-            act[k] = act[k] && cur[k] != it;
-            if (act[k]) act[k] = atomicExch(&stamp[d[k]], it) != it;
-            far[k] = far[k] && cur[k] == 0u;
-            if (far[k]) far[k] = atomicExch(&far_flag[d[k]], 1u) == 0u;
+            act[k] = act[k] && was[k] != it;
+            far[k] = far[k] && was[k] == 0u;
         }
     }
 };
@@ -306,14 +337,16 @@ struct SsspParentOp {
     const int32_t *perm;  // relabelled graph: the smallest CALLER id wins, stored as a caller id
     __device__ __forceinline__ uint32_t vertex_value(int v) const { return dist[v]; }
     __device__ __forceinline__ bool active(uint32_t dv) const { return dv != kInf; }
-    __device__ __forceinline__ void relax(const int (&e)[kU], const int (&d)[kU], const int (&sv)[kU],
+    __device__ __forceinline__ uint32_t edge_value(int e) const { return w[e]; }
+    __device__ __forceinline__ void relax(const uint32_t (&ew)[kU], const int (&d)[kU], const int (&sv)[kU],
                                           const uint32_t (&dv)[kU], bool (&act)[kU], bool (&)[kU],
                                           uint32_t &, uint32_t &, uint32_t &) const {
         uint32_t s[kU], cur[kU];
 #pragma unroll
-        for (int k = 0; k < kU; ++k) s[k] = act[k] ? dv[k] + w[e[k]] : 0u;
+        for (int k = 0; k < kU; ++k) s[k] = dv[k] + ew[k];
 #pragma unroll
         for (int k = 0; k < kU; ++k) cur[k] = act[k] ? dist[d[k]] : 0u;
+        phase(cur);
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
             if (act[k] && d[k] != src && s[k] == cur[k] && s[k] >= dv[k])

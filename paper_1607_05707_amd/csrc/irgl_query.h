@@ -254,6 +254,7 @@ __device__ __forceinline__ void build_pull_bitmaps(const Params &p, uint32_t cur
             const uint32_t v = base + j * blockDim.x + threadIdx.x;
             lv[j] = v < n ? p.val[v] : kInf;
         }
+        phase(lv);
 #pragma unroll
         for (int j = 0; j < kPullV; ++j) {
             const uint32_t v = base + j * blockDim.x + threadIdx.x;
@@ -293,6 +294,7 @@ __device__ __forceinline__ void pull_level(const Params &p, uint32_t next, Team 
             const uint32_t v = base + j * B + threadIdx.x;
             vw[j] = v < n ? p.visited[v >> 5] : ~0u;
         }
+        phase(vw);
 #pragma unroll
         for (int j = 0; j < kPullV; ++j) {
             const uint32_t v = base + j * B + threadIdx.x;
@@ -300,6 +302,8 @@ __device__ __forceinline__ void pull_level(const Params &p, uint32_t next, Team 
             rr0[j] = unvisited ? p.row_ptr[v] : 0;
             rr1[j] = unvisited ? p.row_ptr[v + 1] : 0;
         }
+        phase(rr0);
+        phase(rr1);
 #pragma unroll
         for (int j = 0; j < kPullV; ++j) {
             const uint32_t v = base + j * B + threadIdx.x;
@@ -366,12 +370,12 @@ __device__ __forceinline__ void pull_heavy(const Params &p, const Op &hop, uint3
     bool saw_big = false;
     for (uint32_t base = tm.id * B; base < n; base += tm.size * B) {
         const uint32_t u = base + threadIdx.x;
-        int e[Op::kU], d[Op::kU], sv[Op::kU];
-        uint32_t dv[Op::kU];
+        int d[Op::kU], sv[Op::kU];
+        uint32_t ew[Op::kU], dv[Op::kU];
         bool act[Op::kU], far[Op::kU];
 #pragma unroll
         for (int k = 0; k < Op::kU; ++k) {
-            e[k] = 0;
+            ew[k] = 0;
             d[k] = 0;
             sv[k] = 0;
             dv[k] = 0;
@@ -394,19 +398,22 @@ __device__ __forceinline__ void pull_heavy(const Params &p, const Op &hop, uint3
                 int vb[kPullBatch];
                 uint32_t hb[kPullBatch];
 #pragma unroll
-                for (int k = 0; k < kPullBatch; ++k) vb[k] = x0 + k < r1 ? p.col[x0 + k] : -1;
+                for (int k = 0; k < kPullBatch; ++k) vb[k] = p.col[min(x0 + k, r1 - 1)];
+                phase(vb);
 #pragma unroll
-                for (int k = 0; k < kPullBatch; ++k) hb[k] = vb[k] >= 0 ? p.hstamp[vb[k]] : ~bucket;
+                for (int k = 0; k < kPullBatch; ++k) hb[k] = p.hstamp[vb[k]];
+                phase(hb);
 #pragma unroll
                 for (int k = 0; k < kPullBatch; ++k) {
-                    if (hb[k] != bucket) continue;
+                    if (x0 + k >= r1 || hb[k] != bucket) continue;
                     const int v = vb[k];
                     const uint32_t dvv = p.val[v];
+                    const uint32_t wv = p.w[x0 + k];
                     const unsigned long long c =
-                        static_cast<unsigned long long>(dvv) + static_cast<unsigned long long>(p.w[x0 + k]);
+                        static_cast<unsigned long long>(dvv) + static_cast<unsigned long long>(wv);
                     if (c < best) {
                         best = c;
-                        e[0] = x0 + k;
+                        ew[0] = wv;
                         sv[0] = v;
                         dv[0] = dvv;
                         act[0] = true;
@@ -416,7 +423,7 @@ __device__ __forceinline__ void pull_heavy(const Params &p, const Op &hop, uint3
             d[0] = static_cast<int>(u);
             scanned += static_cast<unsigned long long>(r1 - r0);
         }
-        hop.relax(e, d, sv, dv, act, far, pu.fmin, pu.tries, pu.wins);
+        hop.relax(ew, d, sv, dv, act, far, pu.fmin, pu.tries, pu.wins);
 #pragma unroll
         for (int k = 0; k < Op::kU; ++k) pu.near(act[k], d[k]);
 #pragma unroll

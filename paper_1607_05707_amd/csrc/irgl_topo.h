@@ -42,12 +42,14 @@ struct BfsTopoOp {
     const int32_t *perm;  // relabelled graph: parents are stored as caller ids
     __device__ __forceinline__ uint32_t vertex_value(int v) const { return level[v]; }
     __device__ __forceinline__ bool active(uint32_t lv) const { return lv == cur; }
-    __device__ __forceinline__ void relax(const int (&)[kU], const int (&d)[kU], const int (&sv)[kU],
+    __device__ __forceinline__ uint32_t edge_value(int) const { return 0u; }
+    __device__ __forceinline__ void relax(const uint32_t (&)[kU], const int (&d)[kU], const int (&sv)[kU],
                                           const uint32_t (&)[kU], bool (&act)[kU], bool (&)[kU], uint32_t &,
                                           uint32_t &tries, uint32_t &wins) const {
         uint32_t lv[kU];
 #pragma unroll
         for (int k = 0; k < kU; ++k) lv[k] = act[k] ? level[d[k]] : 0u;
+        phase(lv);
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
             const bool label = act[k] && lv[k] == kInf;
@@ -76,16 +78,15 @@ struct SsspTopoOp {
     Ctrl *ctrl;
     __device__ __forceinline__ uint32_t vertex_value(int v) const { return dist[v]; }
     __device__ __forceinline__ bool active(uint32_t dv) const { return dv != kInf; }
-    __device__ __forceinline__ void relax(const int (&e)[kU], const int (&d)[kU], const int (&)[kU],
+    __device__ __forceinline__ uint32_t edge_value(int e) const { return w[e]; }
+    __device__ __forceinline__ void relax(const uint32_t (&ew)[kU], const int (&d)[kU], const int (&)[kU],
                                           const uint32_t (&dv)[kU], bool (&act)[kU], bool (&)[kU], uint32_t &,
                                           uint32_t &tries, uint32_t &wins) const {
-        uint32_t nd[kU], cur[kU];
-#pragma unroll
-        for (int k = 0; k < kU; ++k) nd[k] = act[k] ? w[e[k]] : 0u;
+        uint32_t nd[kU], cur[kU], old[kU];
         bool ovf = false;
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
-            const uint32_t s = dv[k] + nd[k];
+            const uint32_t s = dv[k] + ew[k];
             const bool bad = act[k] && (s < dv[k] || s == kInf);  // does not fit below INF
             ovf |= bad;
             act[k] = act[k] && !bad;
@@ -94,12 +95,18 @@ struct SsspTopoOp {
         if (ovf) set_error(ctrl, kErrOverflow, false);
 #pragma unroll
         for (int k = 0; k < kU; ++k) cur[k] = act[k] ? dist[d[k]] : 0u;
+        phase(cur);
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
-            const bool try_it = act[k] && nd[k] < cur[k];
-            tries += try_it ? 1u : 0u;
-            const bool won = try_it && nd[k] < atomicMin(&dist[d[k]], nd[k]);
-            wins += won ? 1u : 0u;
+            act[k] = act[k] && nd[k] < cur[k];
+            tries += act[k] ? 1u : 0u;
+            old[k] = no_value();
+            if (act[k]) old[k] = atomicMin(&dist[d[k]], nd[k]);
+        }
+        phase(old);
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            wins += act[k] && nd[k] < old[k] ? 1u : 0u;
             act[k] = false;
         }
     }
