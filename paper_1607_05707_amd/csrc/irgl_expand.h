@@ -470,24 +470,34 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
 // Phase B (grid tier): every workgroup takes an equal contiguous share of
 // the chunks of the deferred vertices (a chunk is B*U edges of one vertex;
 // hub_base[] is ascending because slots and chunk bases come from one
-// packed counter).  Called by all threads of every workgroup.
+// packed counter).  Fewer chunks than workgroups are cut into 2^k pieces
+// each, down to one wavefront's width: a chunk is a thousand scattered
+// probes and claims, which one compute unit issues one after another (a
+// first BFS hub phase on RMAT-22, 8 chunks on 256 workgroups, took 21 us;
+// RMAT-22 BFS 372 against 389 us per query with the pieces).  Called by all threads of every workgroup.
 template <int B, class Op>
 __device__ __forceinline__ void expand_hubs(uint32_t nhubs, uint32_t nchunks, const int32_t *hub_v,
                                             const uint32_t *hub_base,
                                             const int32_t *__restrict__ row_ptr,
                                             const int32_t *__restrict__ col, const Op &op, Smem<B> &sm,
                                             Pushers &pu, Team tm) {
-    constexpr int kChunk = B * Op::kU;
+    uint32_t kChunk = B * Op::kU;  // edges of a unit of work
+    uint32_t cut = 0;              // a chunk is 2^cut units
+    while ((nchunks << (cut + 1)) <= tm.size && kChunk > static_cast<uint32_t>(kWave)) {
+        ++cut;
+        kChunk >>= 1;
+    }
     const unsigned long long G = tm.size;
-    const uint32_t lo = static_cast<uint32_t>(nchunks * static_cast<unsigned long long>(tm.id) / G);
-    const uint32_t hi = static_cast<uint32_t>(nchunks * static_cast<unsigned long long>(tm.id + 1) / G);
+    const unsigned long long units = static_cast<unsigned long long>(nchunks) << cut;
+    const uint32_t lo = static_cast<uint32_t>(units * static_cast<unsigned long long>(tm.id) / G);
+    const uint32_t hi = static_cast<uint32_t>(units * static_cast<unsigned long long>(tm.id + 1) / G);
     if (lo >= hi) return;  // uniform across the workgroup
     if (threadIdx.x == 0) {
-        // the last deferred vertex whose first chunk is <= lo
+        // the last deferred vertex whose first unit is <= lo
         uint32_t a = 0, b = nhubs;
         while (b - a > 1) {
             const uint32_t mid = (a + b) / 2;
-            if (hub_base[mid] <= lo) a = mid;
+            if (hub_base[mid] <= lo >> cut) a = mid;
             else b = mid;
         }
         sm.hub_h = static_cast<int>(a);
@@ -497,13 +507,14 @@ __device__ __forceinline__ void expand_hubs(uint32_t nhubs, uint32_t nchunks, co
     uint32_t c = lo;
     while (c < hi && h < nhubs) {
         const int v = hub_v[h];
-        const uint32_t cb = hub_base[h];
+        const uint32_t cb = hub_base[h] << cut;
         int r0, r1;
         op_range(op, row_ptr, v, r0, r1);
-        const uint32_t nch = static_cast<uint32_t>((r1 - r0 + kChunk - 1) / kChunk);
+        const uint32_t nch = ((static_cast<uint32_t>(r1 - r0) + B * Op::kU - 1) / (B * Op::kU)) << cut;
         const uint32_t c_end = min(hi, cb + nch);
-        const int e_lo = r0 + static_cast<int>((c - cb) * kChunk);
-        const int e_hi = min(r1, r0 + static_cast<int>((c_end - cb) * kChunk));
+        // (the units of a chunk's unused end are empty)
+        const int e_lo = static_cast<int>(min(static_cast<uint32_t>(r1), r0 + (c - cb) * kChunk));
+        const int e_hi = static_cast<int>(min(static_cast<uint32_t>(r1), r0 + (c_end - cb) * kChunk));
         const uint32_t val = op.vertex_value(v);
         stride_range(op, col, e_lo, e_hi, v, val, threadIdx.x, B, pu);
         c = c_end;
