@@ -443,6 +443,33 @@ irgl_status pinned_word(uint32_t **p) {
     return IRGL_OK;
 }
 
+// Deterministic SSSP parents, after the distances.
+template <int B>
+irgl_status parent_pass(const Params &p, hipStream_t s, int kind) {
+    if (kind == IRGL_KIND_SSSP && p.parent) {
+        hipLaunchKernelGGL((sssp_parent_kernel<B>), dim3(fill_grid(p.n, B)), dim3(B), 0, s, p);
+        IRGL_HIP(hipGetLastError());
+    }
+    return IRGL_OK;
+}
+
+// Graphs whose single queries run in one workgroup: no cooperative launch (22
+// us of the 54 us of a query of two invocations), and no grid barrier.  It
+// pays while the largest worklists do not need more compute units: default
+// against a full grid in us per query, BFS 59 / 102 on 8K, 69 / 123 on 53K
+// R-MAT and 108 / 145 on 64K uniform edges, 174 / 171 on 8,000 vertices of
+// degree 4; SSSP 186 / 227 on 8K and 184 / 217 on 12K edges, 307 / 327 on
+// 32K uniform edges but 416 / 274 on others of that size and 533 / 331 on
+// 53K R-MAT edges.
+constexpr int64_t kOneVertices = 1 << 13;
+constexpr int64_t kOneEdges = 1 << 16;
+constexpr int64_t kOneEdgesSssp = 1 << 14;
+bool one_workgroup(const irgl_graph_s *g, const Cfg &c, int kind) {
+    // an explicit grid is kept, and so is a watchdog that ends every wait
+    return g->n <= kOneVertices && g->m <= (kind == IRGL_KIND_SSSP ? kOneEdgesSssp : kOneEdges) && c.grid == 0 &&
+           c.watchdog_ms != IRGL_WATCHDOG_IMMEDIATE;
+}
+
 template <int B, class Op>
 irgl_status launch_query(const irgl_graph_s *g, Params &p, const Cfg &c, hipStream_t s, int kind) {
     DeviceInfo di;
@@ -456,17 +483,29 @@ irgl_status launch_query(const irgl_graph_s *g, Params &p, const Cfg &c, hipStre
     p.abort_flag = c.abort_flag;
     p.barrier = c.barrier;
 
+    // A small graph's query is one ordinary launch of one workgroup, which
+    // fills its arrays itself.
+    const bool one = c.mode == IRGL_MODE_PERSISTENT && one_workgroup(g, c, kind);
+    if (one) {
+        p.fill = kind == IRGL_KIND_SSSP ? 2u : 1u;
+        hipLaunchKernelGGL((persistent_kernel<B, Op, true>), dim3(1), dim3(B), 0, s, p);
+        IRGL_HIP(hipGetLastError());
+        return parent_pass<B>(p, s, kind);
+    }
     hipLaunchKernelGGL(init_kernel, dim3(fill_grid(p.n, 256)), dim3(256), 0, s, p,
                        kind == IRGL_KIND_SSSP ? 1 : 0);
     IRGL_HIP(hipGetLastError());
 
     if (c.mode == IRGL_MODE_PERSISTENT) {
+        // few invocations of a scale-free graph are small: the kernel without
+        // solo runs keeps more registers for the others (RMAT-22 BFS 0.39
+        // against 0.41 ms per query)
+        const auto kernel = scale_free(g) ? persistent_kernel<B, Op, false> : persistent_kernel<B, Op, true>;
         int grid = 0;
-        st = coresident_grid(persistent_kernel<B, Op>, B, g->device, c.grid, &grid);
+        st = coresident_grid(kernel, B, g->device, c.grid, &grid);
         if (st) return st;
         void *args[] = {&p};
-        IRGL_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(persistent_kernel<B, Op>),
-                                            dim3(grid), dim3(B), args, 0, s));
+        IRGL_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(kernel), dim3(grid), dim3(B), args, 0, s));
     } else if (c.mode == IRGL_MODE_TOPOLOGY) {
         using TOp = typename TopoOf<Op>::type;
         int grid = 0;
@@ -533,12 +572,7 @@ irgl_status launch_query(const irgl_graph_s *g, Params &p, const Cfg &c, hipStre
         hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(64), 0, s, p, hit_limit);
         IRGL_HIP(hipGetLastError());
     }
-
-    if (kind == IRGL_KIND_SSSP && p.parent) {
-        hipLaunchKernelGGL((sssp_parent_kernel<B>), dim3(fill_grid(p.n, B)), dim3(B), 0, s, p);
-        IRGL_HIP(hipGetLastError());
-    }
-    return IRGL_OK;
+    return parent_pass<B>(p, s, kind);
 }
 
 template <class Op>
@@ -618,6 +652,7 @@ irgl_status run(int kind, irgl_graph g, int32_t src, uint32_t *out, int32_t *par
     p.do_alpha = c.do_alpha;
     p.do_beta = c.do_beta;
     p.m = g->m;
+    p.solo_items = solo_items(g->n, g->m);
     p.t_bitmap = c.t_bitmap;
     if (kind == IRGL_KIND_SSSP) {
         p.far0 = reinterpret_cast<int32_t *>(base + L.far0);

@@ -114,6 +114,8 @@ __device__ __forceinline__ Params task_params(const BatchParams &bp, const TaskD
     p.pull_open_div = 0;
     p.step_grow = 0;
     p.heavy_m = 0;
+    p.solo_items = solo_items(t.n, __builtin_amdgcn_readfirstlane(t.row_ptr[t.n]));
+    p.fill = 0;
     return p;
 }
 
@@ -146,8 +148,8 @@ __device__ __forceinline__ bool run_task(const BatchParams &bp, const TaskDesc &
     init_arrays(p, td.kind == 1 ? 1 : 0, tm);
     if (leader) init_control(p, false);
     if (!grid_barrier(ctrl, bs, &sm.flag, nullptr, tm)) return false;
-    if (td.kind == 1) r = run_iterate<B, SsspOp>(p, sm, tm, bs);
-    else r = run_iterate<B, BfsOp>(p, sm, tm, bs);
+    if (td.kind == 1) r = run_iterate<B, SsspOp, true>(p, sm, tm, bs);
+    else r = run_iterate<B, BfsOp, true>(p, sm, tm, bs);
     add_block_total<B>(r.edges, &ctrl->edges);
     add_block_total<B>(r.fedges, &ctrl->fedges);
     // every workgroup's edge count and pushes are in before the leader reads them

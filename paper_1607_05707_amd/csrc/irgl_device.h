@@ -82,8 +82,18 @@ struct alignas(128) Ctrl {
     uint32_t hbig[3];
     uint32_t pulls;  // SSSP heavy passes run as a pull
     uint32_t pad4[6];
+    // line 14: loop state after a solo run, rotating like the worklist counters
+    struct Solo {
+        uint32_t it;      // invocations so far
+        uint32_t tr;      // SSSP threshold raises so far
+        uint32_t thresh;  // SSSP threshold
+        uint32_t pad;
+        unsigned long long items;   // items popped so far
+        unsigned long long m_seen;  // out-degree sum of all worklists so far
+    } solo[3];
+    uint32_t pad5[8];
 };
-static_assert(sizeof(Ctrl) == 13 * 128, "control block layout");
+static_assert(sizeof(Ctrl) == 14 * 128, "control block layout");
 
 // Host-visible statistics (layout of irgl_stats).
 struct Stats {
@@ -316,6 +326,15 @@ __device__ __forceinline__ bool grid_barrier(Ctrl *ctrl, BarrierState &bs, int *
                                              const volatile int32_t *abort_flag, Team tm) {
     __builtin_amdgcn_s_waitcnt(0);  // this wave's stores have reached the L2
     __syncthreads();
+    if (tm.size == 1) {  // one workgroup: nothing to wait for, its caches are its own
+        if (threadIdx.x == 0) {
+            if (abort_flag && __hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0)
+                set_error(ctrl, kErrAborted, true);
+            *s_flag = load_agent(&ctrl->fatal) == 0u;
+        }
+        __syncthreads();
+        return *s_flag != 0;
+    }
     if (threadIdx.x == 0) {
         if (bs.epoch == 0 && xcc_id() != blockIdx.x % kBarGroups) atomicOr(&ctrl->xmap_bad, 1u);
         if (abort_flag && tm.id == 0 &&

@@ -41,6 +41,16 @@ struct Pushers {
     __device__ __forceinline__ void far(bool p, int item) {
         fq.push(p, item, skf.cnt_out, skf.out, skf.cap, skf.ctrl);
     }
+    template <int U>
+    __device__ __forceinline__ void push_near(const bool (&p)[U], const int (&item)[U]) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) near(p[k], item[k]);
+    }
+    template <int U>
+    __device__ __forceinline__ void push_far(const bool (&p)[U], const int (&item)[U]) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) far(p[k], item[k]);
+    }
     // All 64 lanes call it (uniform call site); does nothing without a list.
     __device__ __forceinline__ void heavy(bool p, int item) {
         if (skh.cnt_out) hq.push(p, item, skh.cnt_out, skh.out, skh.cap, skh.ctrl);
@@ -175,19 +185,19 @@ __device__ __forceinline__ void drain_all(Pushers &pu, S &sm) {
 // Relax U edges of one lane and push the survivors (all 64 lanes call it).
 // e[k] is a valid entry of the graph also where act[k] is false, so the
 // column and weight loads need no branch of their own.
-template <class Op>
+template <int U, class Op, class P>
 __device__ __forceinline__ void relax_and_push(const Op &op, const int32_t *__restrict__ col,
-                                               const int (&e)[Op::kU], bool (&act)[Op::kU], const int (&sv)[Op::kU],
-                                               const uint32_t (&sval)[Op::kU], Pushers &pu) {
-    int d[Op::kU];
-    uint32_t ew[Op::kU];
-    bool far[Op::kU];
+                                               const int (&e)[U], bool (&act)[U], const int (&sv)[U],
+                                               const uint32_t (&sval)[U], P &pu) {
+    int d[U];
+    uint32_t ew[U];
+    bool far[U];
     bool any = false;
 #pragma unroll
-    for (int k = 0; k < Op::kU; ++k) any |= act[k];
+    for (int k = 0; k < U; ++k) any |= act[k];
     if (__ballot(any) == 0ull) return;  // uniform across the wavefront
 #pragma unroll
-    for (int k = 0; k < Op::kU; ++k) {
+    for (int k = 0; k < U; ++k) {
         d[k] = col[e[k]];
         ew[k] = op.edge_value(e[k]);
         far[k] = false;
@@ -195,10 +205,10 @@ __device__ __forceinline__ void relax_and_push(const Op &op, const int32_t *__re
     phase(d);
     op.relax(ew, d, sv, sval, act, far, pu.fmin, pu.tries, pu.wins);
     // out-degrees of the pushed vertices: read while they are being queued
-    uint32_t lo[Op::kU], hi[Op::kU];
+    uint32_t lo[U], hi[U];
     if (!Op::kFar && pu.deg_rp) {
 #pragma unroll
-        for (int k = 0; k < Op::kU; ++k) {
+        for (int k = 0; k < U; ++k) {
             lo[k] = hi[k] = 0u;
             if (act[k]) {
                 lo[k] = static_cast<uint32_t>(pu.deg_rp[d[k]]);
@@ -206,20 +216,14 @@ __device__ __forceinline__ void relax_and_push(const Op &op, const int32_t *__re
             }
         }
     }
-    if (Op::kPush) {
-#pragma unroll
-        for (int k = 0; k < Op::kU; ++k) pu.near(act[k], d[k]);
-    }
+    if (Op::kPush) pu.push_near(act, d);
     if (!Op::kFar && pu.deg_rp) {
         phase(lo);
         phase(hi);
 #pragma unroll
-        for (int k = 0; k < Op::kU; ++k) pu.mf += static_cast<unsigned long long>(hi[k] - lo[k]);
+        for (int k = 0; k < U; ++k) pu.mf += static_cast<unsigned long long>(hi[k] - lo[k]);
     }
-    if (Op::kFar) {
-#pragma unroll
-        for (int k = 0; k < Op::kU; ++k) pu.far(far[k], d[k]);
-    }
+    if (Op::kFar) pu.push_far(far, d);
 }
 
 // A group of `width` lanes (lane index `li` in it) strides the range
@@ -245,7 +249,7 @@ __device__ __forceinline__ void stride_range(const Op &op, const int32_t *__rest
             act[k] = e[k] < r1;
             e[k] = min(e[k], r1 - 1);
         }
-        relax_and_push(op, col, e, act, svs, svals, pu);
+        relax_and_push<Op::kU>(op, col, e, act, svs, svals, pu);
     }
 }
 
@@ -461,7 +465,7 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
                 sv[k] = sm.vtx[o];
                 sval[k] = sm.vval[o];
             }
-            relax_and_push(op, col, e, act, sv, sval, pu);
+            relax_and_push<Op::kU>(op, col, e, act, sv, sval, pu);
         }
         __syncthreads();  // the scan arrays are rewritten by the next tile
     }
@@ -530,10 +534,10 @@ __device__ __forceinline__ void expand_hubs(uint32_t nhubs, uint32_t nchunks, co
 // ---------------------------------------------------------------------------
 // A vertex moved to the worklist claims its push stamp for invocation `it`,
 // so that a relaxation in the same invocation cannot list it a second time.
-template <int B>
+template <int B, class P>
 __device__ __forceinline__ void far_transfer(const int32_t *far_in, uint32_t far_n, uint32_t n,
                                              uint32_t t_old, uint32_t t_new, const uint32_t *dist,
-                                             uint32_t *far_flag, uint32_t *stamp, uint32_t it, Pushers &pu,
+                                             uint32_t *far_flag, uint32_t *stamp, uint32_t it, P &pu,
                                              Team tm) {
     const uint32_t stride = tm.size * B;
     for (uint32_t base = tm.id * B; base < far_n; base += stride) {

@@ -21,9 +21,18 @@ struct Smem {
     uint32_t vval[B];              // its per-vertex value (SSSP distance at pop)
     int wsum[NW];                  // per-wavefront degree sums for the workgroup scan
     int fill[NW];                  // per-wavefront queue fill at the workgroup drain
-    int queue[NW][kQueueCap];      // worklist (near) staging
-    int queue_far[NW][kQueueCap];  // SSSP far-list staging
-    int queue_heavy[NW][kHeavyQ];  // SSSP heavy-list staging (vertices expanded in the current bucket)
+    union {
+        struct {
+            int queue[NW][kQueueCap];      // worklist (near) staging
+            int queue_far[NW][kQueueCap];  // SSSP far-list staging
+            int queue_heavy[NW][kHeavyQ];  // SSSP heavy-list staging (vertices expanded in the current bucket)
+        };
+        int solo[2][4 * B];  // the two worklists of solo invocations (no queue is in use then)
+    };
+    uint32_t solo_cnt[3];          // solo: rotating worklist counters
+    uint32_t solo_far[2];          // solo: entries of the two far lists ...
+    uint32_t solo_fmin[2];         // ... and lower bounds of their distances
+    unsigned long long solo_sum;   // solo: out-degree sum of the worklist left at the end
     int owner;                     // workgroup-tier vertex owner
     int big_r0, big_r1, big_v;
     uint32_t big_val;
@@ -32,6 +41,7 @@ struct Smem {
     int hub_h;                     // grid tier: first deferred vertex of this workgroup
     uint32_t tile;                 // next worklist tile of this workgroup
 };
+static_assert(8 * 256 <= 256 / kWave * (2 * kQueueCap + kHeavyQ), "the solo worklists fit the queues' space");
 
 struct Params {
     int32_t n;
@@ -113,6 +123,8 @@ struct Params {
     // SSSP with the pull bookkeeping: once 7/8 of the heavy entries have been
     // listed, thresholds rise by step_grow steps at a time; 0 = one step
     uint32_t step_grow;
+    uint32_t solo_items;  // largest worklist of a solo run (irgl_solo.h); 0 = none
+    uint32_t fill;        // 1: the kernel fills a BFS query's arrays itself, 2: an SSSP query's
 };
 
 // ---------------------------------------------------------------------------
@@ -139,28 +151,29 @@ struct BfsOp {
     __device__ __forceinline__ uint32_t vertex_value(int) const { return 0u; }
     __device__ __forceinline__ bool active(uint32_t) const { return true; }
     __device__ __forceinline__ uint32_t edge_value(int) const { return 0u; }
-    __device__ __forceinline__ void relax(const uint32_t (&)[kU], const int (&d)[kU], const int (&sv)[kU],
-                                          const uint32_t (&)[kU], bool (&act)[kU], bool (&)[kU],
+    template <int U>
+    __device__ __forceinline__ void relax(const uint32_t (&)[U], const int (&d)[U], const int (&sv)[U],
+                                          const uint32_t (&)[U], bool (&act)[U], bool (&)[U],
                                           uint32_t &, uint32_t &tries, uint32_t &wins) const {
         // Cheapest filter first: the n/8-byte bitmap stays resident in L2.
         // (visited is null when the bitmap is disabled: a uniform branch)
         if (visited) {
-            uint32_t wd[kU];
+            uint32_t wd[U];
 #pragma unroll
-            for (int k = 0; k < kU; ++k) wd[k] = visited[static_cast<uint32_t>(d[k]) >> 5];
+            for (int k = 0; k < U; ++k) wd[k] = visited[static_cast<uint32_t>(d[k]) >> 5];
             phase(wd);
 #pragma unroll
-            for (int k = 0; k < kU; ++k) act[k] = act[k] && !(wd[k] & (1u << (d[k] & 31)));
+            for (int k = 0; k < U; ++k) act[k] = act[k] && !(wd[k] & (1u << (d[k] & 31)));
         }
         // A plain (possibly stale) load of the level filters most of the rest;
         // stale values can only read INF, and the CAS decides.
-        uint32_t lv[kU];
+        uint32_t lv[U];
 #pragma unroll
-        for (int k = 0; k < kU; ++k) lv[k] = act[k] ? level[d[k]] : 0u;
+        for (int k = 0; k < U; ++k) lv[k] = act[k] ? level[d[k]] : 0u;
         phase(lv);
-        uint32_t old[kU];
+        uint32_t old[U];
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
+        for (int k = 0; k < U; ++k) {
             act[k] = act[k] && lv[k] == kInf;
             tries += act[k] ? 1u : 0u;
             old[k] = no_value();
@@ -168,13 +181,13 @@ struct BfsOp {
         }
         phase(old);
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
+        for (int k = 0; k < U; ++k) {
             act[k] = act[k] && old[k] == kInf;
             wins += act[k] ? 1u : 0u;
         }
         if (parent) {
 #pragma unroll
-            for (int k = 0; k < kU; ++k)
+            for (int k = 0; k < U; ++k)
                 if (act[k]) parent[d[k]] = perm ? perm[sv[k]] : sv[k];
         }
     }
@@ -243,22 +256,23 @@ struct SsspOp {
     __device__ __forceinline__ uint32_t vertex_value(int v) const { return dist[v]; }
     __device__ __forceinline__ bool active(uint32_t) const { return true; }
     __device__ __forceinline__ uint32_t edge_value(int e) const { return w[e]; }
-    __device__ __forceinline__ void relax(const uint32_t (&ew)[kU], const int (&d)[kU], const int (&)[kU],
-                                          const uint32_t (&dv)[kU], bool (&act)[kU],
-                                          bool (&far)[kU], uint32_t &fmin, uint32_t &tries, uint32_t &wins) const {
-        uint32_t nd[kU], cur[kU], old[kU], was[kU];
+    template <int U>
+    __device__ __forceinline__ void relax(const uint32_t (&ew)[U], const int (&d)[U], const int (&)[U],
+                                          const uint32_t (&dv)[U], bool (&act)[U],
+                                          bool (&far)[U], uint32_t &fmin, uint32_t &tries, uint32_t &wins) const {
+        uint32_t nd[U], cur[U], old[U], was[U];
         // a settled destination cannot improve (weights >= 1): skip it with an
         // L2-resident bit test instead of a probe of dist[]
         if (settled) {
 #pragma unroll
-            for (int k = 0; k < kU; ++k) cur[k] = settled[static_cast<uint32_t>(d[k]) >> 5];
+            for (int k = 0; k < U; ++k) cur[k] = settled[static_cast<uint32_t>(d[k]) >> 5];
             phase(cur);
 #pragma unroll
-            for (int k = 0; k < kU; ++k) act[k] = act[k] && !(cur[k] & (1u << (d[k] & 31)));
+            for (int k = 0; k < U; ++k) act[k] = act[k] && !(cur[k] & (1u << (d[k] & 31)));
         }
         bool ovf = false;
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
+        for (int k = 0; k < U; ++k) {
             const uint32_t s = dv[k] + ew[k];
             const bool bad = act[k] && (s < dv[k] || s == kInf);  // does not fit below INF
             ovf |= bad;
@@ -268,14 +282,14 @@ struct SsspOp {
         if (ovf) set_error(ctrl, kErrOverflow, false);
         if (shadow16) {  // uniform
 #pragma unroll
-            for (int k = 0; k < kU; ++k)
+            for (int k = 0; k < U; ++k)
                 cur[k] = act[k] ? reinterpret_cast<const uint16_t *>(shadow)[d[k]] : 0u;
             phase(cur);
 #pragma unroll
-            for (int k = 0; k < kU; ++k) cur[k] = cur[k] == 0xFFFFu ? kInf : cur[k];
+            for (int k = 0; k < U; ++k) cur[k] = cur[k] == 0xFFFFu ? kInf : cur[k];
         } else {
 #pragma unroll
-            for (int k = 0; k < kU; ++k) cur[k] = act[k] ? shadow[d[k]] : 0u;
+            for (int k = 0; k < U; ++k) cur[k] = act[k] ? shadow[d[k]] : 0u;
             phase(cur);
         }
         // The claim, and with it a probe of the word that says whether d is
@@ -284,7 +298,7 @@ struct SsspOp {
         // while listed).  A probe may be older than the claim: a set mark
         // stays set until the list is read, after a barrier.
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
+        for (int k = 0; k < U; ++k) {
             act[k] = act[k] && nd[k] < cur[k];
             tries += act[k] ? 1u : 0u;
             far[k] = act[k] && nd[k] >= thresh;
@@ -292,14 +306,14 @@ struct SsspOp {
             if (act[k]) old[k] = atomicMin(&dist[d[k]], nd[k]);
         }
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
+        for (int k = 0; k < U; ++k) {
             cur[k] = no_value();
             if (act[k]) cur[k] = (far[k] ? far_flag : stamp)[d[k]];
         }
         phase(cur);
         phase(old);
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
+        for (int k = 0; k < U; ++k) {
             const bool won = act[k] && nd[k] < old[k];
             wins += won ? 1u : 0u;
             if (won) {
@@ -316,7 +330,7 @@ struct SsspOp {
         }
         phase(was);
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
+        for (int k = 0; k < U; ++k) {
             act[k] = act[k] && was[k] != it;
             far[k] = far[k] && was[k] == 0u;
         }
@@ -338,17 +352,18 @@ struct SsspParentOp {
     __device__ __forceinline__ uint32_t vertex_value(int v) const { return dist[v]; }
     __device__ __forceinline__ bool active(uint32_t dv) const { return dv != kInf; }
     __device__ __forceinline__ uint32_t edge_value(int e) const { return w[e]; }
-    __device__ __forceinline__ void relax(const uint32_t (&ew)[kU], const int (&d)[kU], const int (&sv)[kU],
-                                          const uint32_t (&dv)[kU], bool (&act)[kU], bool (&)[kU],
+    template <int U>
+    __device__ __forceinline__ void relax(const uint32_t (&ew)[U], const int (&d)[U], const int (&sv)[U],
+                                          const uint32_t (&dv)[U], bool (&act)[U], bool (&)[U],
                                           uint32_t &, uint32_t &, uint32_t &) const {
-        uint32_t s[kU], cur[kU];
+        uint32_t s[U], cur[U];
 #pragma unroll
-        for (int k = 0; k < kU; ++k) s[k] = dv[k] + ew[k];
+        for (int k = 0; k < U; ++k) s[k] = dv[k] + ew[k];
 #pragma unroll
-        for (int k = 0; k < kU; ++k) cur[k] = act[k] ? dist[d[k]] : 0u;
+        for (int k = 0; k < U; ++k) cur[k] = act[k] ? dist[d[k]] : 0u;
         phase(cur);
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
+        for (int k = 0; k < U; ++k) {
             if (act[k] && d[k] != src && s[k] == cur[k] && s[k] >= dv[k])
                 atomicMin(reinterpret_cast<uint32_t *>(&parent[d[k]]),
                           static_cast<uint32_t>(perm ? perm[sv[k]] : sv[k]));

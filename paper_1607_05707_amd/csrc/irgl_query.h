@@ -3,7 +3,7 @@
 // the SSSP parent pass and the on-device CSR validation.
 #pragma once
 
-#include "irgl_expand.h"
+#include "irgl_solo.h"
 
 namespace irgl {
 
@@ -450,7 +450,7 @@ struct LoopResult {
     uint32_t pulls;             // SSSP heavy passes run as a pull (uniform)
 };
 
-template <int B, class Op>
+template <int B, class Op, bool kSolo>
 __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, Team tm, BarrierState &bs) {
     const int tid = threadIdx.x;
     const int wid = tid / kWave;
@@ -473,7 +473,7 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
     if (can_pull) pu.deg_rp = p.row_ptr;
     const int32_t *in = p.wl0;
     int32_t *out = p.wl1;
-    uint32_t it = 0;
+    uint32_t it = 0;                              // invocations so far
     uint32_t tr = 0;                              // threshold raises so far
     uint32_t thresh = Op::kFar ? p.delta : kInf;  // near/far split point
     const bool lead = tm.id == 0 && tid == 0;
@@ -482,8 +482,16 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
     unsigned long long refreshed = 0;
     unsigned long long hdone = 0;  // heavy edges of the buckets drained so far
 
-    for (;; ++it) {
-        uint32_t cnt_in = load_agent(&ctrl->cnt[it % 3]);
+    // Solo runs (irgl_solo.h) need the plain worklists: not on a split graph,
+    // whose expansions also list vertices for the heavy pass, and not with a
+    // settled bitmap.  A team invocation follows each, so that a worklist the
+    // first workgroup leaves (too many items or edges) makes progress.
+    const bool can_solo = kSolo && p.solo_items > 0 && !split && !(Op::kFar && p.visited);
+    bool solo_next = can_solo;
+    uint32_t rot = 0;  // rotates the counters: team invocations and solo runs so far
+
+    for (;;) {
+        uint32_t cnt_in = load_agent(&ctrl->cnt[rot % 3]);
         if (cnt_in > p.cap) cnt_in = p.cap;  // overflowed pushes were dropped (error set)
         uint32_t far_n = 0, nheavy = 0;
         if (cnt_in == 0) {
@@ -496,15 +504,86 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
             if (lead) set_error(ctrl, kErrIterLimit, false);
             break;
         }
+        // uniform: settled counters.  The out-degree sum of the worklist, where
+        // it is known, says beforehand that one workgroup is not enough.
+        const bool solo =
+            kSolo && solo_next && cnt_in > 0 && cnt_in <= p.solo_items &&
+            (!can_pull || __hip_atomic_load(&ctrl->mf[rot % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= kSoloEdges);
+        if (lead) {
+            store_agent(&ctrl->cnt[(rot + 2) % 3], 0u);
+            store_agent(&ctrl->tile[(rot + 2) % 3], 0u);
+            __hip_atomic_store(&ctrl->hub[(rot + 2) % 3], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&ctrl->mf[(rot + 2) % 3], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // read inside invocation rot after a barrier of it: clear the next one's
+            store_agent(&ctrl->hbig[(rot + 1) % 3], 0u);
+        }
+        if constexpr (kSolo) {
+            if (solo) {
+                // To every other workgroup the whole run is one invocation: it pops
+                // counter rot, leaves counter rot + 1 and ends with a team barrier,
+                // so no word that a late workgroup still reads is written early.
+                Ctrl::Solo *const slot = &ctrl->solo[rot % 3];
+                if (tm.id == 0) {
+                    SoloState st{it, tr, thresh, r.items, m_seen, r.max_frontier};
+                    const unsigned long long edges_before = r.edges;
+                    unsigned long long edges_traced = r.edges;
+                    const uint32_t left = solo_run<B, Op>(
+                        in, cnt_in, out, p.cap, static_cast<uint32_t>(p.n), p.row_ptr, p.col, p.val, p.expd, p.far_flag,
+                        p.stamp, p.far0, p.far1, p.far_cap, p.delta, p.max_iter, ctrl, sm, st, r.edges,
+                        [&](uint32_t i, uint32_t th, uint32_t t) {
+                            Op op = make_op<Op>(p, i, th, t, false);
+                            if constexpr (!Op::kFar) op.visited = nullptr;  // the claim alone: one round trip less
+                            return op;
+                        },
+                        [&](uint32_t i, uint32_t items) {
+                            const bool on = tracing(p, i);
+                            if (on && tid == 0) trace_start(p, i, items);
+                            return on;
+                        },
+                        [&](uint32_t i, unsigned long long e, unsigned long long busy, SoloPushers &spu) {
+                            trace_level(p, i, e - edges_traced, &ctrl->hub[rot % 3], Team{0u, 1u}, spu, busy);
+                            edges_traced = e;  // (no vertex is deferred: the grid-tier counter is 0)
+                        });
+                    r.fedges += r.edges - edges_before;
+                    r.max_frontier = st.max_frontier;
+                    if (tid == 0) {
+                        store_agent(&ctrl->cnt[(rot + 1) % 3], left);
+                        if (Op::kFar) {
+                            store_agent(&ctrl->far_cnt[st.tr % 3], sm.solo_far[st.tr & 1u]);
+                            store_agent(&ctrl->far_min[st.tr % 3], sm.solo_fmin[st.tr & 1u]);
+                            store_agent(&ctrl->far_cnt[(st.tr + 1) % 3], 0u);
+                            store_agent(&ctrl->far_min[(st.tr + 1) % 3], kInf);
+                        } else {
+                            __hip_atomic_store(&ctrl->mf[(rot + 1) % 3], sm.solo_sum, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                        }
+                        store_agent(&slot->it, st.it);
+                        store_agent(&slot->tr, st.tr);
+                        store_agent(&slot->thresh, st.thresh);
+                        __hip_atomic_store(&slot->items, st.items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        __hip_atomic_store(&slot->m_seen, st.m_seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
+                if (!grid_barrier(ctrl, bs, &sm.flag, p.abort_flag, tm)) break;
+                it = load_agent(&slot->it);
+                tr = load_agent(&slot->tr);
+                thresh = load_agent(&slot->thresh);
+                r.items = __hip_atomic_load(&slot->items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                m_seen = __hip_atomic_load(&slot->m_seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                bitmaps_current = false;
+                pull = false;
+                solo_next = false;
+                ++rot;
+                const int32_t *t = in;
+                in = out;
+                out = const_cast<int32_t *>(t);
+                continue;
+            }
+        }
+        solo_next = can_solo;
         r.items += cnt_in;
         r.max_frontier = max(r.max_frontier, cnt_in);
         if (lead) {
-            store_agent(&ctrl->cnt[(it + 2) % 3], 0u);
-            store_agent(&ctrl->tile[(it + 2) % 3], 0u);
-            __hip_atomic_store(&ctrl->hub[(it + 2) % 3], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&ctrl->mf[(it + 2) % 3], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            // read inside invocation it after a barrier of it: clear the next one's
-            store_agent(&ctrl->hbig[(it + 1) % 3], 0u);
             if (cnt_in == 0) {
                 store_agent(&ctrl->far_cnt[(tr + 2) % 3], 0u);
                 store_agent(&ctrl->far_min[(tr + 2) % 3], kInf);
@@ -514,8 +593,8 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
             }
             if (tracing(p, it)) trace_start(p, it, cnt_in);
         }
-        pu.sk = Sink{&ctrl->cnt[(it + 1) % 3], out, p.cap, ctrl};
-        unsigned long long *hub_ctr = &ctrl->hub[it % 3];
+        pu.sk = Sink{&ctrl->cnt[(rot + 1) % 3], out, p.cap, ctrl};
+        unsigned long long *hub_ctr = &ctrl->hub[rot % 3];
         if (cnt_in == 0) {
             // transfer invocation (SSSP only): far list tr -> next worklist / far list tr + 1.
             // With an empty far list (only a heavy pass left) the threshold
@@ -569,20 +648,20 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
                           (p.pull_open_div == 0 || hs * p.pull_open_div >= open);
             bool pulled = false;
             if (pull_h) {
-                if constexpr (Op::kFar) pull_heavy<B, Op>(p, hop, lo, tr, tm, pu, r.edges, &ctrl->hbig[it % 3]);
+                if constexpr (Op::kFar) pull_heavy<B, Op>(p, hop, lo, tr, tm, pu, r.edges, &ctrl->hbig[rot % 3]);
                 drain_all<B, Op>(pu, sm);
                 if (!grid_barrier(ctrl, bs, &sm.flag, p.abort_flag, tm)) break;
                 // an unsettled vertex with a long heavy range was left out: the
                 // push pass relaxes every listed vertex's heavy edges after all
                 // (the pull's relaxations were real edges: nothing to undo)
-                pulled = load_agent(&ctrl->hbig[it % 3]) == 0u;
+                pulled = load_agent(&ctrl->hbig[rot % 3]) == 0u;
                 r.pulls += pulled ? 1u : 0u;
             }
             if (!pulled) {
                 if (nheavy > 0)
                     expand<B, Op>(p.hlist, nheavy, static_cast<uint32_t>(p.n), p.row_ptr, p.col, hop, sm, pu,
                                   p.t_wave, p.t_block, p.t_grid, p.hub_v, p.hub_base, p.hub_cap, hub_ctr, r.edges, tm,
-                                  &ctrl->tile[it % 3]);
+                                  &ctrl->tile[rot % 3]);
                 drain_all<B, Op>(pu, sm);
                 if (!grid_barrier(ctrl, bs, &sm.flag, p.abort_flag, tm)) break;
                 if (nheavy > 0 && p.t_grid > 0) {
@@ -601,7 +680,7 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
             ++tr;
         } else if (can_pull && ([&] {
                        // uniform: the settled out-degree sum of this worklist
-                       m_f = __hip_atomic_load(&ctrl->mf[it % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                       m_f = __hip_atomic_load(&ctrl->mf[rot % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                        m_seen += m_f;
                        const long long m_u = p.m - static_cast<long long>(m_seen);
                        if (!pull) pull = static_cast<long long>(m_f) * p.do_alpha > m_u;
@@ -611,7 +690,7 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
                        return pull;
                    }())) {
             // bottom-up invocation: bitmaps, barrier, pull
-            pu.mf_out = &ctrl->mf[(it + 1) % 3];
+            pu.mf_out = &ctrl->mf[(rot + 1) % 3];
             if (!bitmaps_current) {
                 build_pull_bitmaps(p, it, tm, fr_cur);
                 if (!grid_barrier(ctrl, bs, &sm.flag, p.abort_flag, tm)) break;
@@ -644,7 +723,7 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
             pu.skh = split ? Sink{&ctrl->hcnt[tr % 3], p.hlist, p.hcap, ctrl, nullptr} : Sink{};
             pu.hsum_out = (split && p.pull_heavy_div) ? &ctrl->hsum[tr % 3] : nullptr;
             pu.hmin_out = &ctrl->hmin[tr % 3];
-            pu.mf_out = &ctrl->mf[(it + 1) % 3];
+            pu.mf_out = &ctrl->mf[(rot + 1) % 3];
             const unsigned long long edges_before = r.edges;
             if (!Op::kFar && p.visited && r.items - refreshed >= p.t_bitmap) {
                 refresh_bitmap(p, tm, kInf);  // BFS: visited = labelled
@@ -655,7 +734,7 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
             unsigned long long busy_a = tr_on ? wall_clock64() : 0ull, busy_b = 0;
             expand<B, Op>(in, cnt_in, static_cast<uint32_t>(p.n), p.row_ptr, p.col, op, sm, pu, p.t_wave,
                           p.t_block, p.t_grid, p.hub_v, p.hub_base, p.hub_cap, hub_ctr, r.edges, tm,
-                          &ctrl->tile[it % 3]);
+                          &ctrl->tile[rot % 3]);
             drain_all<B, Op>(pu, sm);
             if (tr_on) busy_a = wall_clock64() - busy_a;
             if (!grid_barrier(ctrl, bs, &sm.flag, p.abort_flag, tm)) break;
@@ -678,6 +757,8 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
         const int32_t *t = in;
         in = out;
         out = const_cast<int32_t *>(t);
+        ++it;
+        ++rot;
     }
     r.iterations = it;
     return r;
@@ -721,14 +802,22 @@ __device__ __forceinline__ void map_to_caller(const Params &p, Team tm) {
     }
 }
 
-// One query per cooperative launch: the whole grid is the team.
-template <int B, class Op>
+// One query per launch: the whole grid is the team.  (Cooperative, unless it
+// is one workgroup: a cooperative launch waits about 11 us for the stream's
+// earlier work and holds up its later work as long.)
+template <int B, class Op, bool kSolo>
 __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(fit_waves<B, Op::kMinWaves>()))) void persistent_kernel(
     Params p) {
     __shared__ Smem<B> sm;
     const Team tm = whole_grid();
     BarrierState bs = make_barrier_state(p.wd_ticks, p.barrier);
-    const LoopResult r = run_iterate<B, Op>(p, sm, tm, bs);
+    if (kSolo && p.fill) {  // a launch of one workgroup
+        init_arrays(p, p.fill == 2u ? 1 : 0, tm);
+        if (threadIdx.x == 0) init_control(p, true);
+        __builtin_amdgcn_s_waitcnt(0);  // the words read past the L1 below are in the L2
+        __syncthreads();
+    }
+    const LoopResult r = run_iterate<B, Op, kSolo>(p, sm, tm, bs);
     // every value is final: the loop ended after a barrier that followed the
     // last write of any workgroup
     if (p.inv) map_to_caller(p, tm);

@@ -43,15 +43,16 @@ struct BfsTopoOp {
     __device__ __forceinline__ uint32_t vertex_value(int v) const { return level[v]; }
     __device__ __forceinline__ bool active(uint32_t lv) const { return lv == cur; }
     __device__ __forceinline__ uint32_t edge_value(int) const { return 0u; }
-    __device__ __forceinline__ void relax(const uint32_t (&)[kU], const int (&d)[kU], const int (&sv)[kU],
-                                          const uint32_t (&)[kU], bool (&act)[kU], bool (&)[kU], uint32_t &,
+    template <int U>
+    __device__ __forceinline__ void relax(const uint32_t (&)[U], const int (&d)[U], const int (&sv)[U],
+                                          const uint32_t (&)[U], bool (&act)[U], bool (&)[U], uint32_t &,
                                           uint32_t &tries, uint32_t &wins) const {
-        uint32_t lv[kU];
+        uint32_t lv[U];
 #pragma unroll
-        for (int k = 0; k < kU; ++k) lv[k] = act[k] ? level[d[k]] : 0u;
+        for (int k = 0; k < U; ++k) lv[k] = act[k] ? level[d[k]] : 0u;
         phase(lv);
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
+        for (int k = 0; k < U; ++k) {
             const bool label = act[k] && lv[k] == kInf;
             tries += label ? 1u : 0u;
             wins += label ? 1u : 0u;
@@ -79,13 +80,14 @@ struct SsspTopoOp {
     __device__ __forceinline__ uint32_t vertex_value(int v) const { return dist[v]; }
     __device__ __forceinline__ bool active(uint32_t dv) const { return dv != kInf; }
     __device__ __forceinline__ uint32_t edge_value(int e) const { return w[e]; }
-    __device__ __forceinline__ void relax(const uint32_t (&ew)[kU], const int (&d)[kU], const int (&)[kU],
-                                          const uint32_t (&dv)[kU], bool (&act)[kU], bool (&)[kU], uint32_t &,
+    template <int U>
+    __device__ __forceinline__ void relax(const uint32_t (&ew)[U], const int (&d)[U], const int (&)[U],
+                                          const uint32_t (&dv)[U], bool (&act)[U], bool (&)[U], uint32_t &,
                                           uint32_t &tries, uint32_t &wins) const {
-        uint32_t nd[kU], cur[kU], old[kU];
+        uint32_t nd[U], cur[U], old[U];
         bool ovf = false;
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
+        for (int k = 0; k < U; ++k) {
             const uint32_t s = dv[k] + ew[k];
             const bool bad = act[k] && (s < dv[k] || s == kInf);  // does not fit below INF
             ovf |= bad;
@@ -94,10 +96,10 @@ struct SsspTopoOp {
         }
         if (ovf) set_error(ctrl, kErrOverflow, false);
 #pragma unroll
-        for (int k = 0; k < kU; ++k) cur[k] = act[k] ? dist[d[k]] : 0u;
+        for (int k = 0; k < U; ++k) cur[k] = act[k] ? dist[d[k]] : 0u;
         phase(cur);
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
+        for (int k = 0; k < U; ++k) {
             act[k] = act[k] && nd[k] < cur[k];
             tries += act[k] ? 1u : 0u;
             old[k] = no_value();
@@ -105,7 +107,7 @@ struct SsspTopoOp {
         }
         phase(old);
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
+        for (int k = 0; k < U; ++k) {
             wins += act[k] && nd[k] < old[k] ? 1u : 0u;
             act[k] = false;
         }
