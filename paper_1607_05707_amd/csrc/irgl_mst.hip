@@ -58,6 +58,11 @@ namespace mst {
 constexpr unsigned long long kNoKey = ~0ull;
 constexpr int kTBlock = 4096;   // ... this many or more: the whole workgroup
 constexpr int kMstQueue = 256;  // LDS push staging per wavefront
+constexpr int kMstU = 4;        // entries per lane per step: their columns and weights, then their
+                                // components, are in flight together (phase() in irgl_device.h)
+constexpr int kMstChase = 32;   // hooks a root follows in one pass
+constexpr int kMstSample = 256; // entries sampled for the dominant component
+constexpr int kMstShare = 64;   // ... which holds at least this many of them
 
 struct MstParams {
     int32_t n;
@@ -75,6 +80,10 @@ struct MstParams {
     int32_t *wl0, *wl1;          // worklists of vertices that still had a cross edge
     int32_t *forest;             // emitted forest edges (canonical entries), capacity n
     int32_t *repmin;             // per root: smallest vertex id of its tree
+    // per vertex: the row key and the canonical entry of the lightest cross
+    // edge found last (in arrays that this lock kind does not use)
+    unsigned long long *best;
+    int32_t *bestentry;
     uint8_t *in_forest;          // optional: per CSR entry, 1 for both directions of forest edges
     int32_t *comp_out;           // optional: smallest vertex id of each vertex's tree
     unsigned long long *weight;  // forest weight (device)
@@ -90,7 +99,7 @@ struct MstParams {
 // The launch reuses control-block counters: cnt[] for the rotating worklist
 // counts, red[] for the pointer-jumping reduction, bu_scan for the number of
 // emitted forest edges.
-__device__ __forceinline__ unsigned long long *forest_count(Ctrl *c) { return &c->bu_scan; }
+__device__ __forceinline__ uint32_t *forest_count(Ctrl *c) { return reinterpret_cast<uint32_t *>(&c->bu_scan); }
 
 template <int B>
 struct MstSmem {
@@ -110,6 +119,7 @@ struct MstSmem {
     int gr0[B];
     int gv[B];
     int gc[B];
+    int sample[kMstSample];
     unsigned long long vmin[B];  // per row: lightest cross edge as (w << 32 | neighbour)
 };
 
@@ -118,16 +128,54 @@ struct MstSmem {
 // smaller endpoint u < v, an edge to u > v has v.  So a row's lightest cross
 // edge is the minimum of the 64-bit row key w << 32 | u.
 
-// Row key minimum of entries [r0, r1) of vertex v in component c, entries
-// first, first + step, ...
-__device__ __forceinline__ unsigned long long scan_row(const MstParams &p, int v, int c, int r0, int r1, int first,
-                                                       int step, unsigned long long &scanned) {
+// The row key of entry k of a lane's kMstU entries, folded into `fold`, for
+// those that lead to another component.  In the first round every vertex is
+// its own component, so the components need no look at memory.
+template <class Fold>
+__device__ __forceinline__ void cross_entries(const MstParams &p, const int (&e)[kMstU], const bool (&act)[kMstU],
+                                              const int (&v)[kMstU], const int (&c)[kMstU], bool first, Fold fold) {
+    int u[kMstU], cu[kMstU];
+    uint32_t w[kMstU];
+#pragma unroll
+    for (int k = 0; k < kMstU; ++k) {
+        u[k] = p.col[e[k]];
+        w[k] = p.w[e[k]];
+    }
+    phase(u);
+    if (first) {  // uniform
+#pragma unroll
+        for (int k = 0; k < kMstU; ++k) cu[k] = u[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < kMstU; ++k) cu[k] = p.comp[u[k]];
+        phase(cu);
+    }
+    phase(w);
+#pragma unroll
+    for (int k = 0; k < kMstU; ++k)
+        if (act[k] && u[k] != v[k] && cu[k] != c[k])
+            fold(k, (static_cast<unsigned long long>(w[k]) << 32) | static_cast<uint32_t>(u[k]));
+}
+
+// Row key minimum of entries [r0, r1) of vertex v in component c, this
+// thread's share of a workgroup's B threads.
+template <int B>
+__device__ __forceinline__ unsigned long long scan_row(const MstParams &p, int v, int c, int r0, int r1, int tid,
+                                                       bool first, unsigned long long &scanned) {
     unsigned long long b = kNoKey;
-    for (int e = r0 + first; e < r1; e += step) {
-        const int u = p.col[e];
-        ++scanned;
-        if (u == v || p.comp[u] == c) continue;
-        b = min(b, (static_cast<unsigned long long>(p.w[e]) << 32) | static_cast<uint32_t>(u));
+    for (int x = r0; x < r1; x += B * kMstU) {
+        int e[kMstU], vs[kMstU], cs[kMstU];
+        bool act[kMstU];
+#pragma unroll
+        for (int k = 0; k < kMstU; ++k) {
+            e[k] = x + k * B + tid;
+            act[k] = e[k] < r1;
+            scanned += act[k] ? 1u : 0u;
+            e[k] = min(e[k], r1 - 1);
+            vs[k] = v;
+            cs[k] = c;
+        }
+        cross_entries(p, e, act, vs, cs, first, [&](int, unsigned long long key) { b = min(b, key); });
     }
     return b;
 }
@@ -247,6 +295,41 @@ __device__ __forceinline__ unsigned long long block_sum(MstSmem<B> &sm, unsigned
     return t;
 }
 
+// A vertex of the component that most of a fixed sample of the entries lead
+// to, if that is a quarter of them or more, else -1.  Every workgroup finds
+// the same one.
+template <int B>
+__device__ __forceinline__ int dominant(const MstParams &p, MstSmem<B> &sm) {
+    static_assert(B >= kMstSample && kMstSample % kWave == 0, "one thread per sample");
+    const int tid = threadIdx.x;
+    const uint32_t m = static_cast<uint32_t>(p.row_ptr[p.n]);
+    if (m == 0u) return -1;  // uniform
+    int u = 0, c = -1, best = 0;
+    if (tid < kMstSample) {
+        const uint32_t e = static_cast<uint32_t>((static_cast<unsigned long long>(tid) * 0x9E3779B97F4A7C15ull >> 32) *
+                                                     static_cast<unsigned long long>(m) >> 32);
+        u = p.col[e];
+        c = p.comp[u];
+        sm.sample[tid] = c;
+    }
+    __syncthreads();
+    if (tid < kMstSample) {
+        for (int k = 0; k < kMstSample; ++k) best += sm.sample[k] == c ? 1 : 0;
+        best = best << 16 | tid;  // ties: the last sample
+    }
+    unsigned long long top = ~0ull - static_cast<unsigned long long>(best);
+    top = wave_min(top);
+    if (lane_id() == 0) sm.red[tid / kWave] = top;
+    __syncthreads();
+    for (int k = 0; k < B / kWave; ++k) top = min(top, sm.red[k]);
+    const int got = static_cast<int>(~0ull - top);
+    if (tid == (got & 0xFFFF)) sm.owner = u;
+    __syncthreads();
+    const int x = sm.owner;
+    __syncthreads();
+    return (got >> 16) >= kMstShare ? x : -1;
+}
+
 // Phase 1 over worklist `in` (identity when null) of cnt_in vertices; pushes
 // the vertices that have a cross edge.  Rows of kTBlock or more entries are
 // scanned by the whole workgroup one at a time; the other rows of a tile are
@@ -255,20 +338,37 @@ __device__ __forceinline__ unsigned long long block_sum(MstSmem<B> &sm, unsigned
 template <int B>
 __device__ __forceinline__ void find_min_edges(const MstParams &p, MstSmem<B> &sm, Team tm, const int32_t *in,
                                                uint32_t cnt_in, WaveQueue<kMstQueue> &wq, uint32_t *cnt_out,
-                                               int32_t *out, unsigned long long &scanned) {
+                                               int32_t *out, unsigned long long &scanned, int skip) {
     constexpr int NW = B / kWave;
     const int tid = threadIdx.x, lane = lane_id(), wid = tid / kWave;
+    const bool first = in == nullptr;  // every vertex is its own component
     for (uint32_t base = tm.id * B; base < cnt_in; base += tm.size * B) {
         const uint32_t i = base + tid;
         int v = -1, c = -1, r0 = 0, r1 = 0;
+        unsigned long long rk = kNoKey;
+        bool kept = false;
         if (i < cnt_in) {
             v = in ? in[i] : static_cast<int>(i);
             c = p.comp[v];
             r0 = p.row_ptr[v];
             r1 = p.row_ptr[v + 1];
+            if (!first) {
+                // the lightest cross edge of the round before is the lightest
+                // still, if it is a cross edge still: cross edges only get
+                // fewer (RMAT-20: rounds 2 and 3 scanned every row again, 300
+                // us each)
+                rk = p.best[v];
+                kept = p.comp[static_cast<uint32_t>(rk)] != c;
+            }
+            if (c == skip) {  // the others will reach it
+                v = -1;
+                kept = false;
+                r1 = r0;
+            }
+            if (kept) r1 = r0;
+            else rk = kNoKey;
         }
         int deg = r1 - r0;
-        unsigned long long rk = kNoKey;
         // workgroup tier: one large row at a time
         while (__syncthreads_or(deg >= kTBlock)) {
             if (deg >= kTBlock) sm.owner = tid;
@@ -281,7 +381,7 @@ __device__ __forceinline__ void find_min_edges(const MstParams &p, MstSmem<B> &s
             }
             __syncthreads();
             const int bv = sm.big_v;
-            const unsigned long long b = wave_min(scan_row(p, bv, p.comp[bv], sm.big_r0, sm.big_r1, tid, B, scanned));
+            const unsigned long long b = wave_min(scan_row<B>(p, bv, p.comp[bv], sm.big_r0, sm.big_r1, tid, first, scanned));
             if (lane == 0) sm.red[wid] = b;
             __syncthreads();
             if (sm.owner == tid) {
@@ -305,23 +405,54 @@ __device__ __forceinline__ void find_min_edges(const MstParams &p, MstSmem<B> &s
         sm.gv[tid] = v;
         sm.gc[tid] = c;
         __syncthreads();
-        for (int done = 0; done < total; done += B) {
-            const int slot = done + tid;
-            if (slot < total) {
-                int o = 0;
+        // a lane takes kMstU consecutive slots, mostly of one row: it folds
+        // them in a register and touches the row's minimum once (an LDS
+        // atomic per entry, most of a wavefront's on one row, was the bound)
+        for (int done = 0; done < total; done += B * kMstU) {
+            int e[kMstU], o[kMstU], vs[kMstU], cs[kMstU];
+            bool act[kMstU];
+            const int s0 = done + tid * kMstU;
+            int ow = 0;
+            if (s0 < total) {
 #pragma unroll
                 for (int step = B / 2; step > 0; step >>= 1)
-                    if (sm.gstart[o + step] <= slot) o += step;
-                const int e = sm.gr0[o] + (slot - sm.gstart[o]);
-                const int u = p.col[e];
-                ++scanned;
-                if (u != sm.gv[o] && p.comp[u] != sm.gc[o])
-                    atomicMin(&sm.vmin[o], (static_cast<unsigned long long>(p.w[e]) << 32) | static_cast<uint32_t>(u));
+                    if (sm.gstart[ow + step] <= s0) ow += step;
             }
+#pragma unroll
+            for (int k = 0; k < kMstU; ++k) {
+                const int slot = s0 + k;
+                act[k] = slot < total;
+                while (act[k] && ow < B - 1 && sm.gstart[ow + 1] <= slot) ++ow;
+                o[k] = ow;
+                e[k] = act[k] ? sm.gr0[ow] + (slot - sm.gstart[ow]) : 0;
+                vs[k] = sm.gv[ow];
+                cs[k] = sm.gc[ow];
+                scanned += act[k] ? 1u : 0u;
+            }
+            int row = o[0];
+            unsigned long long low = kNoKey;
+            cross_entries(p, e, act, vs, cs, first, [&](int k, unsigned long long key) {
+                if (o[k] != row) {
+                    if (low != kNoKey) atomicMin(&sm.vmin[row], low);
+                    row = o[k];
+                    low = kNoKey;
+                }
+                low = min(low, key);
+            });
+            if (low != kNoKey) atomicMin(&sm.vmin[row], low);
         }
         __syncthreads();
         if (deg > 0) rk = sm.vmin[tid];
-        unsigned long long k = v >= 0 ? candidate_key(p, v, rk) : kNoKey;
+        unsigned long long k = kNoKey;
+        if (kept) {
+            k = (rk & 0xFFFFFFFF00000000ull) | static_cast<uint32_t>(p.bestentry[v]);
+        } else if (v >= 0) {
+            k = candidate_key(p, v, rk);
+            if (k != kNoKey) {
+                p.best[v] = rk;
+                p.bestentry[v] = static_cast<int32_t>(static_cast<uint32_t>(k));
+            }
+        }
         const bool has = k != kNoKey;
         // Cooperative conversion of the atomic section: the candidates of the
         // wavefront's lanes that share the first candidate lane's component
@@ -359,6 +490,15 @@ __global__ __launch_bounds__(B) void mst_kernel(MstParams p) {
     unsigned long long scanned = 0, items = 0, added = 0;
     uint32_t round = 0;
     uint32_t jumps = 0;  // pointer-jumping passes so far (rotates the reduction words)
+    // A vertex of the component that holds most entries, once there is one.
+    // That component chooses no edge from then on: every other component
+    // still chooses its lightest, so each joins another and the forest is the
+    // same, but its rows (nearly all of the graph in the last rounds, whose
+    // vertices would find no edge to another component) are not scanned.  The
+    // same vertex names it in every round, so its vertices may leave the
+    // worklist for good.
+    int x0 = -1;
+    uint32_t *const fcnt = forest_count(ctrl);
     bool ok = true;
     for (;; ++round) {
         const uint32_t cnt_in = round == 0 ? n : min(load_agent(&ctrl->cnt[round % 3]), n);
@@ -373,11 +513,14 @@ __global__ __launch_bounds__(B) void mst_kernel(MstParams p) {
         int32_t *out = (round & 1u) ? p.wl0 : p.wl1;
         WaveQueue<kMstQueue> wq{sm.queue[wid], 0};
         // phase 1: find-min-edge with the atomic section
-        find_min_edges<B>(p, sm, tm, in, cnt_in, wq, &ctrl->cnt[(round + 1) % 3], out, scanned);
+        if (round > 0 && x0 < 0) x0 = dominant<B>(p, sm);
+        find_min_edges<B>(p, sm, tm, in, cnt_in, wq, &ctrl->cnt[(round + 1) % 3], out, scanned,
+                          x0 < 0 ? -2 : p.comp[x0]);
         block_drain<B, kMstQueue>(wq, sm.fill, &sm.base, &ctrl->cnt[(round + 1) % 3], out, n, ctrl);
         if (!(ok = grid_barrier(ctrl, bs, &sm.flag, nullptr, tm))) break;
-        // phase 2: hook every root with a candidate, emit its edge (the
-        // wavefront reserves its forest slots with one atomic)
+        // phase 2: hook every root with a candidate, emit its edge through the
+        // wavefront's LDS queue (one atomic per wavefront and step on the one
+        // forest counter was 0.18 of the phase's 0.21 ms on RMAT-20)
         for (uint32_t base2 = tm.id * B; base2 < n; base2 += stride) {
             const uint32_t c = base2 + threadIdx.x;
             bool emit = false;
@@ -395,17 +538,14 @@ __global__ __launch_bounds__(B) void mst_kernel(MstParams p) {
                     if (emit) added += static_cast<unsigned long long>(k >> 32);
                 }
             }
-            const unsigned long long em = __ballot(emit);
-            if (em) {
-                unsigned long long slot0 = 0;
-                if (lane_id() == 0) slot0 = atomicAdd(forest_count(ctrl), static_cast<unsigned long long>(__popcll(em)));
-                slot0 = __shfl(slot0, 0, kWave);
-                const unsigned long long slot = slot0 + lane_rank(em);
-                if (emit && slot < n) p.forest[slot] = e;
-            }
+            wq.push(emit, e, fcnt, p.forest, n, ctrl);
         }
+        block_drain<B, kMstQueue>(wq, sm.fill, &sm.base, fcnt, p.forest, n, ctrl);
         if (!(ok = grid_barrier(ctrl, bs, &sm.flag, nullptr, tm))) break;
-        // phase 3: pointer jumping over the hooks, While Any(changed)
+        // phase 3: pointer jumping over the hooks, While Any(unfinished): a
+        // root follows its hooks for up to kMstChase steps, which ends most
+        // phases after one pass (concurrent writes only put an ancestor
+        // nearer the end in place of another)
         for (uint32_t pass = 0;; ++jumps, ++pass) {
             // the hooks form a forest (edge keys strictly fall along a hook
             // chain), so its depth is below n and log2 n passes flatten it
@@ -421,12 +561,14 @@ __global__ __launch_bounds__(B) void mst_kernel(MstParams p) {
             bool changed = false;
             for (uint32_t c = gid; c < n; c += stride) {
                 if (p.comp[c] != static_cast<int32_t>(c)) continue;
-                const int32_t h = p.hook[c];
-                const int32_t hh = p.hook[h];
-                if (hh != h) {
-                    p.hook[c] = hh;
-                    changed = true;
+                const int32_t h0 = p.hook[c];
+                int32_t h = h0, hh = p.hook[h0];
+                for (int k = 0; k < kMstChase && hh != h; ++k) {
+                    h = hh;
+                    hh = p.hook[h];
                 }
+                if (h != h0) p.hook[c] = h;
+                changed |= hh != h;
             }
             if (__syncthreads_or(changed) && threadIdx.x == 0) atomicOr(red, 1u);
             if (!(ok = grid_barrier(ctrl, bs, &sm.flag, nullptr, tm))) break;
@@ -462,27 +604,36 @@ __global__ __launch_bounds__(B) void mst_kernel(MstParams p) {
     }
     if (ok) ok = grid_barrier(ctrl, bs, &sm.flag, nullptr, tm);
     if (ok) {
-        // smallest vertex id of every tree, then the per-entry marks
-        // (consecutive lanes hold consecutive ids: the first lane of each run
-        // of one component holds its smallest id in the wavefront)
+        // smallest vertex id of every tree, then the per-entry marks.  The
+        // dominant component's is one minimum per thread and one atomic per
+        // wavefront (its 620,000 atomics on one word took 2.9 ms of 6.3 on
+        // RMAT-20); of the others a wavefront's lanes that share the first
+        // lane's component leave it to that lane (consecutive lanes hold
+        // consecutive ids), and a lane whose id is no smaller than the word
+        // it reads, which only falls, has nothing to do.
+        if (x0 < 0) x0 = dominant<B>(p, sm);
+        const int32_t big = x0 < 0 ? -2 : p.comp[x0];
+        uint32_t low = kInf;
         for (uint32_t base3 = tm.id * B; base3 < n; base3 += stride) {
             const uint32_t v = base3 + threadIdx.x;
             const bool live = v < n;
             const int cv = live ? p.comp[v] : -1;
-            const unsigned long long lm = __ballot(live);
-            bool mine = live;
+            bool mine = live && cv != big;
+            if (live && !mine) low = min(low, v);
+            const unsigned long long lm = __ballot(mine);
             if (lm) {
                 const int leader = __ffsll(static_cast<long long>(lm)) - 1;
                 const int cl = __shfl(cv, leader, kWave);
-                if (live && cv == cl && lane_id() != leader) mine = false;
+                if (cv == cl && lane_id() != leader) mine = false;
             }
-            if (mine) atomicMin(&p.repmin[cv], static_cast<int32_t>(v));
+            if (mine && static_cast<int32_t>(v) < p.repmin[cv]) atomicMin(&p.repmin[cv], static_cast<int32_t>(v));
         }
-        const unsigned long long nf = min(__hip_atomic_load(forest_count(ctrl), __ATOMIC_RELAXED,
-                                                            __HIP_MEMORY_SCOPE_AGENT),
-                                          static_cast<unsigned long long>(n));
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) low = min(low, static_cast<uint32_t>(__shfl_xor(low, off, kWave)));
+        if (lane_id() == 0 && low != kInf) atomicMin(&p.repmin[big], static_cast<int32_t>(low));
+        const uint32_t nf = min(load_agent(fcnt), n);
         if (p.in_forest) {
-            for (unsigned long long k = gid; k < nf; k += stride) {
+            for (uint32_t k = gid; k < nf; k += stride) {
                 const int e = p.forest[k];
                 const int lo = row_of(p, e), hi = p.col[e];
                 p.in_forest[e] = 1;
@@ -508,7 +659,7 @@ __global__ __launch_bounds__(B) void mst_kernel(MstParams p) {
             s->grid = static_cast<int32_t>(tm.size);
             s->block = B;
             s->heavy_pulls = 0;
-            s->frontier_edges = __hip_atomic_load(forest_count(ctrl), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s->frontier_edges = load_agent(fcnt);
         }
     }
 }
@@ -565,7 +716,7 @@ MstLayout mst_layout(int64_t n) {
     L.hook = L.comp + nb;
     L.key = L.hook + nb;
     L.minwt = L.key + align_b(static_cast<size_t>(n) * 8);
-    L.minedge = L.minwt + nb;
+    L.minedge = L.minwt + nb;  // (the two hold n 64-bit words for the packed kind)
     L.lock = L.minedge + nb;
     L.ticket = L.lock + nb;
     L.serving = L.ticket + nb;
@@ -669,6 +820,8 @@ irgl_status irgl_mst(irgl_graph g, uint64_t *weight, int32_t *component, uint8_t
     p.wl1 = reinterpret_cast<int32_t *>(base + L.wl1);
     p.forest = reinterpret_cast<int32_t *>(base + L.forest);
     p.repmin = reinterpret_cast<int32_t *>(base + L.repmin);
+    p.best = reinterpret_cast<unsigned long long *>(base + (kind == IRGL_LOCK_PACKED ? L.minwt : L.key));
+    p.bestentry = reinterpret_cast<int32_t *>(base + (kind == IRGL_LOCK_SPIN ? L.ticket : L.lock));
     p.in_forest = in_forest;
     p.comp_out = component;
     p.weight = reinterpret_cast<unsigned long long *>(weight);
