@@ -304,12 +304,12 @@ irgl_status resolve(const irgl_graph_s *g, int kind, const irgl_config *c, Cfg *
                                     : (kind == IRGL_KIND_SSSP ? IRGL_BITMAP_NEVER : default_t_bitmap(g->n, g->m));
     // direction optimization needs in-edges = out-edges and the outlined loop
     const bool sym = (g->flags & IRGL_SYMMETRIC) != 0;
-    r.do_alpha = (c && c->do_alpha) ? c->do_alpha : 14u;
+    r.do_alpha = (c && c->do_alpha) ? c->do_alpha : kDoAlpha;
     // back to top-down below n / 96 frontier vertices (16 sources, us per
     // query at 24 / 48 / 96 / 192: RMAT-20 234 / 230 / 229 / 229, RMAT-21
     // 310 / 308 / 308 / 305, RMAT-22 366 / 363 / 360 / 360, RMAT-23 565 /
     // 557 / 558 / 558, road 4096^2 unchanged)
-    r.do_beta = (c && c->do_beta) ? c->do_beta : 96u;
+    r.do_beta = (c && c->do_beta) ? c->do_beta : kDoBeta;
     if (!sym || r.do_alpha == IRGL_DO_OFF || r.mode != IRGL_MODE_PERSISTENT) r.do_alpha = 0;
     r.trace_len = (c && c->trace) ? c->trace_len : 0u;
     r.trace = (c && c->trace) ? reinterpret_cast<unsigned long long *>(c->trace) : nullptr;
@@ -786,7 +786,8 @@ void region_layout(int64_t nmax, int64_t mmax, bool any_sssp, int t_grid, int bl
     L->off_far1 = o;  o += any_sssp ? nb : 0;
     L->off_far_flag = o;  o += any_sssp ? nb : 0;
     L->off_expd = o;  o += any_sssp ? nb : 0;
-    L->off_visited = o;  o += align_up((static_cast<size_t>(nmax) + 31) / 32 * 4);
+    // visited bitmap, and the two frontier bitmaps of bottom-up BFS
+    L->off_visited = o;  o += 3 * align_up((static_cast<size_t>(nmax) + 31) / 32 * 4);
     L->off_hub_v = o;  o += align_up(static_cast<size_t>(L->hub_cap) * 4);
     L->off_hub_base = o;  o += align_up(static_cast<size_t>(L->hub_cap) * 4);
     L->team_bytes = align_up(o);
@@ -884,6 +885,7 @@ uint32_t task_delta(const irgl_graph_s *g, uint32_t override_delta);
 void fill_desc(TaskDesc &d, const irgl_task &t, Stats *stats, uint32_t delta_override, bool gang = false) {
     std::memset(&d, 0, sizeof(d));
     d.gang = gang ? 1u : 0u;
+    d.pull = t.kind == IRGL_KIND_BFS && (t.g->flags & IRGL_SYMMETRIC) ? 1u : 0u;
     d.row_ptr = t.g->orig_row_ptr;
     d.col = t.g->orig_col;
     d.w = t.g->orig_w;

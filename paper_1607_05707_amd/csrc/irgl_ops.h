@@ -9,6 +9,8 @@ namespace irgl {
 
 constexpr int kQueueCap = 256;  // LDS staging entries per wavefront
 constexpr int kHeavyQ = 64;     // LDS staging entries per wavefront for the SSSP heavy list
+constexpr uint32_t kDoAlpha = 14;  // BFS direction choice (irgl_config.do_alpha, do_beta)
+constexpr uint32_t kDoBeta = 96;
 constexpr int kUMax = 4;        // largest edges-per-lane-per-round of any operator
 
 // Shared-memory layout of the frontier kernels for workgroup size B.
