@@ -128,8 +128,9 @@ typedef struct irgl_graph_s *irgl_graph;
  * the grid and gather tiers are used; the workgroup and wavefront tiers take
  * ranges when their thresholds are set. */
 typedef struct irgl_config {
-    int32_t block;        /* threads per workgroup: 256, 512 or 1024 (default: 1024
-                             for BFS, 512 for SSSP) */
+    int32_t block;        /* threads per workgroup: 256, 512 or 1024 (default: 512;
+                             1024 for BFS on scale-free graphs from 2^26 edges,
+                             with an explicit grid, and not outlined) */
     int32_t t_wave;       /* wavefront tier threshold, >= 1 (default: t_block, or 64
                              when t_block is set) */
     int32_t t_block;      /* workgroup tier threshold, >= t_wave (default: t_grid) */
@@ -139,7 +140,10 @@ typedef struct irgl_config {
                              t_block) for outlined SSSP; lowered to
                              block for a worklist with fewer items than the grid has
                              threads); IRGL_GRID_TIER_OFF = never */
-    int32_t grid;         /* workgroups; 0 = co-resident limit (occupancy x CUs) */
+    int32_t grid;         /* workgroups; 0 = the co-resident limit (occupancy x CUs),
+                             or, with block 0 too, fewer on graphs whose
+                             invocations cost more in barriers than they gain
+                             from it; one, in an ordinary launch, on the smallest */
     int32_t mode;         /* IRGL_MODE_* */
     uint32_t max_iter;    /* safety cap on invocations (default n + 1 for BFS,
                              4n + 16 for SSSP, whose threshold raises also count) */

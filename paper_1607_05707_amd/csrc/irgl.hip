@@ -235,6 +235,7 @@ struct Cfg {
     uint32_t trace_len;
     unsigned long long *trace;
     uint32_t delta;
+    int most_grid;  // default shape: workgroups at most (0: the co-resident limit)
     uint32_t do_alpha, do_beta;  // do_alpha == 0: no bottom-up invocations
     uint32_t barrier;
     uint32_t reduce;  // topology-driven loop: IRGL_REDUCE_*
@@ -260,7 +261,55 @@ void resolve_tiers(int block, int t_wave, int t_block, int t_grid, int *ow, int 
 // Default workgroup size per kind, from sweeps over road and RMAT graphs:
 // BFS invocations are short, and 1024-thread workgroups cut the barrier
 // arrivals per invocation fourfold; SSSP's longer invocations do best at 512.
-int default_block(int kind) { return kind == IRGL_KIND_BFS ? 1024 : 512; }
+// Default launch shape of outlined single queries (block and grid both left
+// at 0).  More workgroups relax more edges at a time but cost every barrier:
+// each drops its caches at the end, one after another on an XCD's L2 (3.6 us
+// per barrier at 256 workgroups, 5.3 at 512).  Measured, us per query at
+// workgroups x threads:
+//   BFS, symmetric: R-MAT 13-17 (0.2-2.9M entries) 100-110 at 64x512, 106-117
+//   at 128, 119-130 at 256, 134-142 at 256x1024; R-MAT 19 (12M) 169 / 167 /
+//   200 / 220; R-MAT 20 (31M) 263 / 223 / 243 / 304; R-MAT 21 (64M) 565 / 357
+//   / 301 / 318; uniform 600,000 x 12 273 / 266 / 283 / 315, 2^20 x 16 900 /
+//   563 / 445 / 508; road-like 400^2 412 / 419 / 457 / 596, 1200^2 939 / 825
+//   / 906 / 1084, 4096^2 - / 4188 / 3307 / 3588;
+//   BFS, directed: 100,000 x 6 181 / 177 / 175, 600,000 x 5 417 / 313 / 279,
+//   1.5M x 11 962 / 614 / 439 / 439;
+//   SSSP at 512 threads and 128 / 256 / 512 workgroups: R-MAT 15 405 / 397 /
+//   472, road-like 400^2 926 / 968 / 1094, uniform 40,000 x 16 507 / 543 /
+//   607; uniform 600,000 x 12 1092 / 1017 / 1145, 2^20 x 16 1802 / 1468 /
+//   1587, 2M x 24 3263 / 2591 / 2503, road-like 2048^2 2637 / 2575 / 2785,
+//   4096^2 9326 / 6825 / 6863; R-MAT 17 751 / 607 / 614, 19 1361 / 977 / 912,
+//   20 2959 / 1911 / 1676; with the light/heavy split R-MAT 18 481 / 490 /
+//   578, 20 818 / 686 / 787, 22 2122 / 1615 / 1574.
+constexpr int64_t kShapeTiny = int64_t(1) << 20;
+constexpr int64_t kShapeSmall = int64_t(1) << 23;
+constexpr int64_t kShapeSmallSkewed = int64_t(1) << 25;
+// Scale-free graphs of this many entries keep BFS at 1024 threads.
+constexpr int64_t kWideBfsMinEdges = int64_t(1) << 26;
+constexpr int64_t kShapeSsspSkewed = int64_t(1) << 22;
+constexpr int64_t kShapeSsspEven = int64_t(1) << 25;
+constexpr int64_t kShapeSsspSplit = int64_t(1) << 26;
+
+int default_block(const irgl_graph_s *g, int kind, const irgl_config *c) {
+    if (kind != IRGL_KIND_BFS) return 512;
+    if (c && (c->grid || c->mode != IRGL_MODE_PERSISTENT)) return 1024;
+    return scale_free(g) && g->m >= kWideBfsMinEdges ? 1024 : 512;
+}
+
+// Workgroups of that shape (0: the co-resident limit).
+int default_workgroups(const irgl_graph_s *g, int kind, bool split) {
+    const int64_t m = g->m;
+    const bool sym = (g->flags & IRGL_SYMMETRIC) != 0;
+    if (kind == IRGL_KIND_BFS) {
+        if (m <= kShapeTiny) return sym ? 64 : 128;
+        if (!sym) return 256;
+        return m <= (scale_free(g) ? kShapeSmallSkewed : kShapeSmall) ? 128 : 256;
+    }
+    if (m <= kShapeTiny) return 128;
+    if (split) return m <= kShapeSsspSplit ? 256 : 0;
+    if (scale_free(g)) return m <= kShapeSsspSkewed ? 256 : 0;
+    return m <= kShapeSsspEven || m < 8 * static_cast<int64_t>(g->n) ? 256 : 0;
+}
 
 // Default grid-tier threshold of single queries, whatever the workgroup size
 // (RMAT-22 SSSP at 512-thread workgroups: 4.73 ms per query at 512 against
@@ -274,9 +323,11 @@ constexpr int kGridTier = 512;
 // 7.83; topology-driven queries lose at 256, see above).
 constexpr int kGridTierSssp = 256;
 
+bool uses_split(const irgl_graph_s *g, int kind, const Cfg &c);
+
 irgl_status resolve(const irgl_graph_s *g, int kind, const irgl_config *c, Cfg *out) {
     Cfg r;
-    r.block = (c && c->block) ? c->block : default_block(kind);
+    r.block = (c && c->block) ? c->block : default_block(g, kind, c);
     if (r.block != 256 && r.block != 512 && r.block != 1024) return IRGL_ERR_CONFIG;
     r.mode = c ? c->mode : IRGL_MODE_PERSISTENT;
     if (r.mode != IRGL_MODE_PERSISTENT && r.mode != IRGL_MODE_HOST_LOOP && r.mode != IRGL_MODE_TOPOLOGY)
@@ -317,6 +368,9 @@ irgl_status resolve(const irgl_graph_s *g, int kind, const irgl_config *c, Cfg *
     r.delta = (c && c->delta) ? c->delta : default_delta(g);
     r.barrier = c ? c->barrier : IRGL_BARRIER_XCD;
     if (r.barrier > IRGL_BARRIER_WORKGROUP) return IRGL_ERR_CONFIG;
+    r.most_grid = 0;
+    if (!(c && c->block) && r.grid == 0 && r.mode == IRGL_MODE_PERSISTENT)
+        r.most_grid = default_workgroups(g, kind, uses_split(g, kind, r));
     *out = r;
     return IRGL_OK;
 }
@@ -458,16 +512,18 @@ irgl_status parent_pass(const Params &p, hipStream_t s, int kind) {
 // pays while the largest worklists do not need more compute units: default
 // against a full grid in us per query, BFS 59 / 102 on 8K, 69 / 123 on 53K
 // R-MAT and 108 / 145 on 64K uniform edges, 174 / 171 on 8,000 vertices of
-// degree 4; SSSP 186 / 227 on 8K and 184 / 217 on 12K edges, 307 / 327 on
-// 32K uniform edges but 416 / 274 on others of that size and 533 / 331 on
-// 53K R-MAT edges.
+// degree 4; SSSP 186 / 227 on 8K uniform edges, 422 / 479 on the 64x64 grid,
+// but 416 / 274 on 32K uniform edges and 533 / 331 on 53K R-MAT edges.
 constexpr int64_t kOneVertices = 1 << 13;
 constexpr int64_t kOneEdges = 1 << 16;
-constexpr int64_t kOneEdgesSssp = 1 << 14;
+constexpr int64_t kOneEdgesSssp = 1 << 14;        // mean out-degree below 8 (grids, road-like graphs)
+constexpr int64_t kOneEdgesSsspDense = 1 << 13;  // others
 bool one_workgroup(const irgl_graph_s *g, const Cfg &c, int kind) {
     // an explicit grid is kept, and so is a watchdog that ends every wait
-    return g->n <= kOneVertices && g->m <= (kind == IRGL_KIND_SSSP ? kOneEdgesSssp : kOneEdges) && c.grid == 0 &&
-           c.watchdog_ms != IRGL_WATCHDOG_IMMEDIATE;
+    const int64_t most = kind != IRGL_KIND_SSSP ? kOneEdges
+                         : g->m < 8 * static_cast<int64_t>(g->n) ? kOneEdgesSssp
+                                                                 : kOneEdgesSsspDense;
+    return g->n <= kOneVertices && g->m <= most && c.grid == 0 && c.watchdog_ms != IRGL_WATCHDOG_IMMEDIATE;
 }
 
 template <int B, class Op>
@@ -504,6 +560,7 @@ irgl_status launch_query(const irgl_graph_s *g, Params &p, const Cfg &c, hipStre
         int grid = 0;
         st = coresident_grid(kernel, B, g->device, c.grid, &grid);
         if (st) return st;
+        if (c.most_grid) grid = std::min(grid, c.most_grid);
         void *args[] = {&p};
         IRGL_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(kernel), dim3(grid), dim3(B), args, 0, s));
     } else if (c.mode == IRGL_MODE_TOPOLOGY) {
