@@ -635,7 +635,7 @@ irgl_status irgl_batch_close(irgl_server s);
 
 typedef struct irgl_mst_config {
     int32_t block;        /* 256, 512 (default) or 1024 */
-    int32_t grid;         /* workgroups; 0 = co-resident limit */
+    int32_t grid;         /* workgroups; 0 = the co-resident limit, fewer on small graphs */
     uint32_t lock;        /* IRGL_LOCK_* */
     uint32_t watchdog_ms; /* bound of every barrier and lock wait (default 20000) */
     uint32_t barrier;     /* IRGL_BARRIER_* */

@@ -670,13 +670,16 @@ __global__ void mst_init_kernel(MstParams p, unsigned long long m) {
     for (unsigned long long v = t; v < static_cast<unsigned long long>(p.n); v += stride) {
         p.comp[v] = static_cast<int32_t>(v);
         p.hook[v] = static_cast<int32_t>(v);
-        p.key[v] = kNoKey;
+        p.repmin[v] = 0x7FFFFFFF;
+        if (p.lock_kind == IRGL_LOCK_PACKED) {  // the other arrays are not this kind's
+            p.key[v] = kNoKey;
+            continue;
+        }
         p.minwt[v] = kInf;
         p.minedge[v] = -1;
         p.lock[v] = 0;
         p.ticket[v] = 0;
         p.serving[v] = 0;
-        p.repmin[v] = 0x7FFFFFFF;
     }
     if (p.in_forest)
         for (unsigned long long e = t; e < m; e += stride) p.in_forest[e] = 0;
@@ -749,11 +752,23 @@ irgl_status mst_grid(int dev, int requested, int *grid) {
     return IRGL_OK;
 }
 
+// Workgroups a graph repays: one thread for about twelve entries (four for a
+// vertex), in steps of 32 workgroups; every further one costs each of the
+// three or more barriers of a round (us per forest at 32 / 128 / 512
+// workgroups of 512 threads: R-MAT 13, 158K entries, 217 / 232 / 310; R-MAT
+// 17, 2.9M, 991 / 468 / 481; road-like 150^2 347 / 320 / 437, 1200^2 10694 /
+// 3119 / 1587).
+int mst_workgroups(int64_t n, int64_t m, int block) {
+    const int64_t groups = (m + 4 * n) / 12 / block;
+    return static_cast<int>(std::min<int64_t>(1 << 20, (groups + 31) / 32 * 32 + (groups == 0 ? 32 : 0)));
+}
+
 template <int B>
-irgl_status mst_launch(MstParams &p, int dev, int requested, hipStream_t s) {
+irgl_status mst_launch(MstParams &p, int64_t m, int dev, int requested, hipStream_t s) {
     int grid = 0;
     irgl_status st = mst_grid<B>(dev, requested, &grid);
     if (st) return st;
+    if (!requested) grid = std::min(grid, mst_workgroups(p.n, m, B));
     void *args[] = {&p};
     MST_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(mst_kernel<B>), dim3(grid), dim3(B), args, 0,
                                        s));
@@ -842,9 +857,9 @@ irgl_status irgl_mst(irgl_graph g, uint64_t *weight, int32_t *component, uint8_t
     hipLaunchKernelGGL(mst_init_kernel, dim3(std::max(fill, 1)), dim3(256), 0, s, p, m);
     MST_HIP(hipGetLastError());
     switch (block) {
-        case 256: st = mst_launch<256>(p, dev, cfg ? cfg->grid : 0, s); break;
-        case 512: st = mst_launch<512>(p, dev, cfg ? cfg->grid : 0, s); break;
-        default: st = mst_launch<1024>(p, dev, cfg ? cfg->grid : 0, s); break;
+        case 256: st = mst_launch<256>(p, csr.m, dev, cfg ? cfg->grid : 0, s); break;
+        case 512: st = mst_launch<512>(p, csr.m, dev, cfg ? cfg->grid : 0, s); break;
+        default: st = mst_launch<1024>(p, csr.m, dev, cfg ? cfg->grid : 0, s); break;
     }
     if (cur != dev) (void)hipSetDevice(cur);
     return st;
