@@ -76,6 +76,10 @@ struct irgl_graph_s {
     const int32_t *perm;           // device: internal id -> caller id
     const int32_t *inv;            // device: caller id -> internal id
     std::vector<int32_t> inv_host;  // host: caller id -> internal id
+    // relabelled symmetric graph: the first four neighbours of each vertex
+    // (null otherwise), and the vertices that have any (the first ones; n otherwise)
+    const int32_t *heads = nullptr;
+    int32_t n_act = 0;
     // SSSP copy of a relabelled weighted graph (null otherwise): the rows of
     // (col, w) partitioned into the edges lighter than split_delta, then the
     // rest, each part in id order; split[v] = first heavy edge of row v.
@@ -710,6 +714,8 @@ irgl_status run(int kind, irgl_graph g, int32_t src, uint32_t *out, int32_t *par
     p.do_beta = c.do_beta;
     p.m = g->m;
     p.solo_items = solo_items(g->n, g->m);
+    p.n_act = g->heads ? g->n_act : g->n;
+    p.heads = g->heads;
     p.t_bitmap = c.t_bitmap;
     if (kind == IRGL_KIND_SSSP) {
         p.far0 = reinterpret_cast<int32_t *>(base + L.far0);
@@ -1144,6 +1150,23 @@ __global__ void inverse_kernel(int32_t n, const int32_t *perm, int32_t *inv, int
     for (int32_t i = i0; i < n; i += gridDim.x * blockDim.x) inv[perm[i]] = i;
 }
 
+// The first four neighbours of every vertex in one place (-1: none), and the
+// number of vertices that have any (ids are by decreasing degree).  A
+// bottom-up invocation decides most vertices by these 16 bytes, read in
+// order; the rows themselves cost it a 128-byte line each.
+__global__ void head_rows_kernel(int32_t n, const int32_t *rp, const int32_t *col, int32_t *heads, int32_t *active) {
+    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
+        const int32_t r0 = rp[v], r1 = rp[v + 1];
+        int4 h;
+        h.x = r0 < r1 ? col[r0] : -1;
+        h.y = r0 + 1 < r1 ? col[r0 + 1] : -1;
+        h.z = r0 + 2 < r1 ? col[r0 + 2] : -1;
+        h.w = r0 + 3 < r1 ? col[r0 + 3] : -1;
+        reinterpret_cast<int4 *>(heads)[v] = h;
+        if (r0 < r1 && (v == n - 1 || rp[v + 2] == r1)) *active = v + 1;
+    }
+}
+
 // One wavefront per internal vertex copies its range with relabelled targets.
 __global__ void relabel_edges_kernel(int32_t n, const int32_t *perm, const int32_t *inv, const int32_t *rp,
                                      const int32_t *col, const uint32_t *w, const int32_t *nrp, int32_t *ncol,
@@ -1178,11 +1201,12 @@ irgl_status reorder_layout(int32_t n, int64_t m, bool weighted, ReorderLayout *o
     L.sw = L.scol + (weighted ? align_up(static_cast<size_t>(m) * 4 + 4) : 0);
     L.split = L.sw + (weighted ? align_up(static_cast<size_t>(m) * 4 + 4) : 0);
     L.perm = L.split + (weighted ? nb : 0);
-    L.keys_in = L.perm + nb;
+    L.inv = L.perm + nb;
+    // build scratch, whose space the heads (head_rows_kernel) take afterwards
+    L.keys_in = L.inv + nb;
     L.keys_out = L.keys_in + nb;
     L.ids_in = L.keys_out + nb;
-    L.inv = L.ids_in + nb;
-    L.tmp = L.inv + nb;
+    L.tmp = L.ids_in + nb;
     size_t sort_b = 0, scan_b = 0;
     IRGL_HIP(hipcub::DeviceRadixSort::SortPairsDescending(nullptr, sort_b, static_cast<const uint32_t *>(nullptr),
                                                           static_cast<uint32_t *>(nullptr),
@@ -1431,6 +1455,20 @@ irgl_status irgl_graph_upload_reordered(const irgl_csr *csr, void *store, size_t
     g->orig_w = csr->w;
     g->perm = perm;
     g->inv = inv;
+    g->n_act = n;
+    if ((csr->flags & IRGL_SYMMETRIC) && L.total - L.keys_in >= static_cast<size_t>(n) * 16 + 4) {
+        int32_t *heads = reinterpret_cast<int32_t *>(b + L.keys_in);
+        hipLaunchKernelGGL(head_rows_kernel, dim3(grid), dim3(256), 0, 0, n, nrp, ncol, heads, heads + 4 * static_cast<size_t>(n));
+        hipError_t he = hipGetLastError();
+        int32_t act = n;
+        if (he == hipSuccess && m > 0) he = hipMemcpy(&act, heads + 4 * static_cast<size_t>(n), 4, hipMemcpyDeviceToHost);
+        if (he != hipSuccess) {
+            delete g;
+            return hip_fail(he);
+        }
+        g->n_act = m > 0 ? act : 0;
+        g->heads = heads;
+    }
     if (nw) {
         g->scol = reinterpret_cast<int32_t *>(b + L.scol);
         g->sw = reinterpret_cast<uint32_t *>(b + L.sw);

@@ -120,6 +120,8 @@ __device__ __forceinline__ Params task_params(const BatchParams &bp, const TaskD
     p.heavy_m = 0;
     p.solo_items = solo_items(t.n, m);
     p.fill = 0;
+    p.n_act = t.n;
+    p.heads = nullptr;
     return p;
 }
 

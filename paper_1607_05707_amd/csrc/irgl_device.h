@@ -154,6 +154,22 @@ __device__ __forceinline__ void phase(int (&x)[U]) {
     phase(reinterpret_cast<uint32_t (&)[U]>(x));
 }
 
+// Four consecutive words p[i..i+3] of an array of `len` as one 16-byte load
+// (any 4-byte alignment), or p[min(i + k, last)] one by one near the array's
+// end.  A lane that walks a row by itself spends one address on them instead
+// of four; what lies past its row is the caller's to ignore.
+__device__ __forceinline__ void load4(const int32_t *p, int i, long long len, int last, int (&x)[4]) {
+    typedef int quad __attribute__((ext_vector_type(4), aligned(4)));
+    if (static_cast<long long>(i) + 4 <= len) {
+        const quad q = *reinterpret_cast<const quad *>(p + i);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = q[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = p[min(i + k, last)];
+    }
+}
+
 // Number of set bits of `mask` below this lane (the lane's rank among the
 // active predicates of its wavefront).
 __device__ __forceinline__ uint32_t lane_rank(unsigned long long mask) {

@@ -125,6 +125,11 @@ struct Params {
     // SSSP with the pull bookkeeping: once 7/8 of the heavy entries have been
     // listed, thresholds rise by step_grow steps at a time; 0 = one step
     uint32_t step_grow;
+    // bottom-up invocations look at the vertices below n_act (the others have
+    // no edges), and first at heads[4 v ..]: the first four neighbours of v,
+    // -1 for none (null: in the row)
+    int32_t n_act;
+    const int32_t *heads;
     uint32_t solo_items;  // largest worklist of a solo run (irgl_solo.h); 0 = none
     uint32_t fill;        // 1: the kernel fills a BFS query's arrays itself, 2: an SSSP query's
 };

@@ -112,7 +112,7 @@ __device__ __forceinline__ BfsOp make_op<BfsOp>(const Params &p, uint32_t it, ui
 // vertices.  Readers may see old or new words concurrently; both only ever
 // mark vertices that qualify, so any mix is a valid filter.
 __device__ __forceinline__ void refresh_bitmap(const Params &p, Team tm, uint32_t below) {
-    const uint32_t n = static_cast<uint32_t>(p.n);
+    const uint32_t n = static_cast<uint32_t>(p.n_act);
     const uint32_t stride = tm.size * blockDim.x;
     for (uint32_t base = tm.id * blockDim.x; base < n; base += stride) {
         const uint32_t v = base + threadIdx.x;
@@ -244,7 +244,7 @@ constexpr int kPullV = 4;
 // base + j * blockDim.x + t, j < kPullV.  (After a bottom-up invocation the
 // pull pass itself leaves both bitmaps current.)
 __device__ __forceinline__ void build_pull_bitmaps(const Params &p, uint32_t cur, Team tm, uint32_t *frontier) {
-    const uint32_t n = static_cast<uint32_t>(p.n);
+    const uint32_t n = static_cast<uint32_t>(p.n_act);
     const uint32_t step = blockDim.x * kPullV;
     const int lane = lane_id();
     for (uint32_t base = tm.id * step; base < n; base += tm.size * step) {
@@ -284,7 +284,7 @@ template <int B>
 __device__ __forceinline__ void pull_level(const Params &p, uint32_t next, Team tm, Pushers &pu,
                                            unsigned long long &scanned, const uint32_t *frontier,
                                            uint32_t *next_frontier) {
-    const uint32_t n = static_cast<uint32_t>(p.n);
+    const uint32_t n = static_cast<uint32_t>(p.n_act);
     constexpr uint32_t kStep = B * kPullV;
     for (uint32_t base = tm.id * kStep; base < n; base += tm.size * kStep) {
         uint32_t vw[kPullV];
@@ -302,26 +302,64 @@ __device__ __forceinline__ void pull_level(const Params &p, uint32_t next, Team 
             rr0[j] = unvisited ? p.row_ptr[v] : 0;
             rr1[j] = unvisited ? p.row_ptr[v + 1] : 0;
         }
-        phase(rr0);
-        phase(rr1);
+        // the first neighbours of all kPullV vertices together: most vertices
+        // that a large frontier reaches are found there (a relabelled graph's
+        // rows begin with its hubs)
+        int first[kPullV];
+        {
+            int u[kPullV][kUMax];
+            uint32_t fw[kPullV][kUMax];
+#pragma unroll
+            for (int j = 0; j < kPullV; ++j) {
+#pragma unroll
+                for (int k = 0; k < kUMax; ++k) u[j][k] = 0;
+                const uint32_t v = base + j * B + threadIdx.x;
+                if (p.heads) {  // uniform
+                    if (v < n && !((vw[j] >> (v & 31)) & 1u)) {
+                        const int4 h = reinterpret_cast<const int4 *>(p.heads)[v];
+                        u[j][0] = h.x;
+                        u[j][1] = h.y;
+                        u[j][2] = h.z;
+                        u[j][3] = h.w;
+                    }
+                } else if (rr0[j] < rr1[j]) {
+                    load4(p.col, rr0[j], p.m, rr1[j] - 1, u[j]);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kPullV; ++j) phase(u[j]);
+#pragma unroll
+            for (int j = 0; j < kPullV; ++j)
+#pragma unroll
+                for (int k = 0; k < kUMax; ++k)
+                    fw[j][k] = rr0[j] + k < rr1[j] ? frontier[static_cast<uint32_t>(u[j][k]) >> 5] : 0u;
+#pragma unroll
+            for (int j = 0; j < kPullV; ++j) {
+                phase(fw[j]);
+                first[j] = -1;
+#pragma unroll
+                for (int k = 0; k < kUMax; ++k)
+                    if (first[j] < 0 && ((fw[j][k] >> (u[j][k] & 31)) & 1u)) first[j] = u[j][k];
+                scanned += static_cast<unsigned long long>(min(kUMax, rr1[j] - rr0[j]));
+            }
+        }
 #pragma unroll
         for (int j = 0; j < kPullV; ++j) {
             const uint32_t v = base + j * B + threadIdx.x;
             const int r0 = rr0[j], r1 = rr1[j];
-            int found = -1;
-            for (int e0 = r0; e0 < r1; e0 += kUMax) {
+            int found = first[j];
+            for (int e0 = r0 + kUMax; found < 0 && e0 < r1; e0 += kUMax) {
                 int u[kUMax];
                 uint32_t fw[kUMax];
+                load4(p.col, e0, p.m, r1 - 1, u);
+                phase(u);
 #pragma unroll
-                for (int k = 0; k < kUMax; ++k) u[k] = e0 + k < r1 ? p.col[e0 + k] : -1;
+                for (int k = 0; k < kUMax; ++k) fw[k] = e0 + k < r1 ? frontier[static_cast<uint32_t>(u[k]) >> 5] : 0u;
+                phase(fw);
 #pragma unroll
                 for (int k = 0; k < kUMax; ++k)
-                    fw[k] = u[k] >= 0 ? frontier[static_cast<uint32_t>(u[k]) >> 5] : 0u;
-#pragma unroll
-                for (int k = 0; k < kUMax; ++k)
-                    if (found < 0 && u[k] >= 0 && ((fw[k] >> (u[k] & 31)) & 1u)) found = u[k];
+                    if (found < 0 && ((fw[k] >> (u[k] & 31)) & 1u)) found = u[k];
                 scanned += static_cast<unsigned long long>(min(kUMax, r1 - e0));
-                if (found >= 0) break;
             }
             if (found >= 0) {
                 p.val[v] = next;
@@ -395,10 +433,15 @@ __device__ __forceinline__ void pull_heavy(const Params &p, const Op &hop, uint3
             // bucket-stamp probes, are in flight together (a long range is
             // otherwise one dependent pair of loads per entry)
             for (int x0 = r0; x0 < r1; x0 += kPullBatch) {
-                int vb[kPullBatch];
+                int vb[kPullBatch], va[4], vc[4];
                 uint32_t hb[kPullBatch];
+                load4(p.col, x0, p.m, r1 - 1, va);
+                load4(p.col, min(x0 + 4, r1 - 1), p.m, r1 - 1, vc);
 #pragma unroll
-                for (int k = 0; k < kPullBatch; ++k) vb[k] = p.col[min(x0 + k, r1 - 1)];
+                for (int k = 0; k < 4; ++k) {
+                    vb[k] = va[k];
+                    vb[k + 4] = vc[k];
+                }
                 phase(vb);
 #pragma unroll
                 for (int k = 0; k < kPullBatch; ++k) hb[k] = p.hstamp[vb[k]];
