@@ -197,10 +197,10 @@ __device__ __forceinline__ int wave_inclusive_scan(int x) {
 // and a contiguous copy; at the end of an invocation the whole workgroup
 // drains the remainders of all its wavefronts with ONE atomicAdd.
 // ---------------------------------------------------------------------------
-template <int QCAP>
 struct WaveQueue {
-    int *q;     // this wavefront's LDS staging area, QCAP entries
+    int *q;     // this wavefront's LDS staging area
     int n;      // wave-uniform fill level
+    int qcap;   // its entries
 
     __device__ __forceinline__ void drain(uint32_t *cnt_out, int *out, uint32_t cap, Ctrl *ctrl) {
         if (n == 0) return;
@@ -225,7 +225,7 @@ struct WaveQueue {
         unsigned long long mask = __ballot(pred);
         if (mask == 0ull) return;
         int k = __popcll(mask);
-        if (n + k > QCAP) drain(cnt_out, out, cap, ctrl);
+        if (n + k > qcap) drain(cnt_out, out, cap, ctrl);
         if (pred) q[n + static_cast<int>(lane_rank(mask))] = item;
         __builtin_amdgcn_wave_barrier();
         n += k;
@@ -234,8 +234,8 @@ struct WaveQueue {
 
 // Workgroup-wide drain of every wavefront queue with a single global atomic.
 // s_fill: LDS int[NW]; s_base: LDS uint32.  Must be called by all threads.
-template <int B, int QCAP>
-__device__ __forceinline__ void block_drain(WaveQueue<QCAP> &wq, int *s_fill, uint32_t *s_base,
+template <int B>
+__device__ __forceinline__ void block_drain(WaveQueue &wq, int *s_fill, uint32_t *s_base,
                                             uint32_t *cnt_out, int *out, uint32_t cap, Ctrl *ctrl) {
     constexpr int NW = B / kWave;
     const int wid = threadIdx.x / kWave;

@@ -387,7 +387,7 @@ __device__ int retriangulate(const Params &p, Item &it, int *made) {
 // triangle (push stamp = invocation + 1).  All lanes of a wavefront call it.
 // ---------------------------------------------------------------------------
 struct Out {
-    WaveQueue<kQ> q;
+    WaveQueue q;
     uint32_t *cnt;
     int32_t *buf;
     uint32_t cap;
@@ -408,7 +408,7 @@ struct Smem {
 
 template <int B>
 __device__ __forceinline__ void drain(Out &o, Smem &sm) {
-    block_drain<B, kQ>(o.q, sm.fill, &sm.base, o.cnt, o.buf, o.cap, o.ctrl);
+    block_drain<B>(o.q, sm.fill, &sm.base, o.cnt, o.buf, o.cap, o.ctrl);
 }
 
 // identify_bad_triangles: a ForAll over every triangle slot in use.
@@ -529,7 +529,7 @@ __global__ __launch_bounds__(B) void dmr_kernel(Params p) {
             break;
         }
         if (lead) store_agent(&p.cnt->out[(inv + 1) % 3], 0u);
-        Out o{{sm.q[wid], 0}, &p.cnt->out[inv % 3], p.wl[in_b ^ 1], p.tcap, p.ctrl, inv + 1};
+        Out o{{sm.q[wid], 0, kQ}, &p.cnt->out[inv % 3], p.wl[in_b ^ 1], p.tcap, p.ctrl, inv + 1};
         const int32_t *in = p.wl[in_b];
         if (stage == 0 || stage == 3) identify<B>(p, tm, o);
         else if (stage == 1) ok = refine<B>(p, in, in_n, tm, bs, sm, o, inv * 0x9E3779B9u);

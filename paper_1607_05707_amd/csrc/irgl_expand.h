@@ -19,8 +19,8 @@ struct Sink {
 
 // The wavefront's staging queues and where they drain to.
 struct Pushers {
-    WaveQueue<kQueueCap> nq;  // outgoing worklist (near)
-    WaveQueue<kQueueCap> fq;  // SSSP far list
+    WaveQueue nq;  // outgoing worklist (near)
+    WaveQueue fq;  // SSSP far list
     Sink sk;
     Sink skf;
     uint32_t fmin;            // this lane's far-list lower bound since the last drain
@@ -29,7 +29,7 @@ struct Pushers {
     unsigned long long mf;    // this lane's sum of out-degrees of pushed vertices
     uint32_t tries = 0;       // this lane's claim atomics (trace statistics)
     uint32_t wins = 0;        // ... and the successful ones
-    WaveQueue<kHeavyQ> hq{nullptr, 0};  // SSSP heavy list of the current bucket
+    WaveQueue hq{nullptr, 0, kHeavyQ};  // SSSP heavy list of the current bucket
     Sink skh{};               // its sink (cnt_out null: no heavy list in this invocation)
     unsigned long long hdeg = 0;           // this lane's heavy out-degrees of listed vertices
     unsigned long long *hsum_out = nullptr;  // ... drained into this per-bucket counter
@@ -136,7 +136,7 @@ __device__ __forceinline__ unsigned long long op_heavy_degree<SsspOp>(const Sssp
 // Workgroup-wide drain of both queues (all threads call it).
 template <int B, class Op, class S>
 __device__ __forceinline__ void drain_all(Pushers &pu, S &sm) {
-    block_drain<B, kQueueCap>(pu.nq, sm.fill, &sm.base, pu.sk.cnt_out, pu.sk.out, pu.sk.cap, pu.sk.ctrl);
+    block_drain<B>(pu.nq, sm.fill, &sm.base, pu.sk.cnt_out, pu.sk.out, pu.sk.cap, pu.sk.ctrl);
     if (pu.deg_rp) {
         // one atomicAdd per wavefront: out-degree sum of the pushed vertices
         unsigned long long x = pu.mf;
@@ -146,7 +146,7 @@ __device__ __forceinline__ void drain_all(Pushers &pu, S &sm) {
         pu.mf = 0;
     }
     if (Op::kFar && pu.skh.cnt_out)  // uniform: the same sink for the whole team
-        block_drain<B, kHeavyQ>(pu.hq, sm.fill, &sm.base, pu.skh.cnt_out, pu.skh.out, pu.skh.cap, pu.skh.ctrl);
+        block_drain<B>(pu.hq, sm.fill, &sm.base, pu.skh.cnt_out, pu.skh.out, pu.skh.cap, pu.skh.ctrl);
     if (Op::kFar && pu.hsum_out) {  // uniform; one atomicAdd and one atomicMin per wavefront
         unsigned long long x = pu.hdeg;
         uint32_t mn = pu.hminv;
@@ -163,7 +163,7 @@ __device__ __forceinline__ void drain_all(Pushers &pu, S &sm) {
     pu.hdeg = 0;
     pu.hminv = kInf;
     if (Op::kFar) {
-        block_drain<B, kQueueCap>(pu.fq, sm.fill, &sm.base, pu.skf.cnt_out, pu.skf.out, pu.skf.cap,
+        block_drain<B>(pu.fq, sm.fill, &sm.base, pu.skf.cnt_out, pu.skf.out, pu.skf.cap,
                                   pu.skf.ctrl);
         // one atomicMin per workgroup for the far-list lower bound
         uint32_t m = pu.fmin;
@@ -270,10 +270,10 @@ __device__ __forceinline__ void stride_range(const Op &op, const int32_t *__rest
 // and the road grid unchanged; 128 and 512 within 1% of 256.
 constexpr int kSmallDefer = 256;
 
-template <int B, class Op>
+template <int B, class Op, class S>
 __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t cnt_in, uint32_t n,
                                        const int32_t *__restrict__ row_ptr,
-                                       const int32_t *__restrict__ col, const Op &op, Smem<B> &sm,
+                                       const int32_t *__restrict__ col, const Op &op, S &sm,
                                        Pushers &pu, int t_wave,
                                        int t_block, int t_grid, int32_t *hub_v, uint32_t *hub_base,
                                        uint32_t hub_cap, unsigned long long *hub_ctr,
@@ -479,11 +479,11 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
 // probes and claims, which one compute unit issues one after another (a
 // first BFS hub phase on RMAT-22, 8 chunks on 256 workgroups, took 21 us;
 // RMAT-22 BFS 372 against 389 us per query with the pieces).  Called by all threads of every workgroup.
-template <int B, class Op>
+template <int B, class Op, class S>
 __device__ __forceinline__ void expand_hubs(uint32_t nhubs, uint32_t nchunks, const int32_t *hub_v,
                                             const uint32_t *hub_base,
                                             const int32_t *__restrict__ row_ptr,
-                                            const int32_t *__restrict__ col, const Op &op, Smem<B> &sm,
+                                            const int32_t *__restrict__ col, const Op &op, S &sm,
                                             Pushers &pu, Team tm) {
     uint32_t kChunk = B * Op::kU;  // edges of a unit of work
     uint32_t cut = 0;              // a chunk is 2^cut units

@@ -337,7 +337,7 @@ __device__ __forceinline__ int dominant(const MstParams &p, MstSmem<B> &sm) {
 // each slot folding its edge into its row's minimum with an LDS atomicMin.
 template <int B>
 __device__ __forceinline__ void find_min_edges(const MstParams &p, MstSmem<B> &sm, Team tm, const int32_t *in,
-                                               uint32_t cnt_in, WaveQueue<kMstQueue> &wq, uint32_t *cnt_out,
+                                               uint32_t cnt_in, WaveQueue &wq, uint32_t *cnt_out,
                                                int32_t *out, unsigned long long &scanned, int skip) {
     constexpr int NW = B / kWave;
     const int tid = threadIdx.x, lane = lane_id(), wid = tid / kWave;
@@ -511,12 +511,12 @@ __global__ __launch_bounds__(B) void mst_kernel(MstParams p) {
         if (lead) store_agent(&ctrl->cnt[(round + 2) % 3], 0u);
         const int32_t *in = round == 0 ? nullptr : ((round & 1u) ? p.wl1 : p.wl0);
         int32_t *out = (round & 1u) ? p.wl0 : p.wl1;
-        WaveQueue<kMstQueue> wq{sm.queue[wid], 0};
+        WaveQueue wq{sm.queue[wid], 0, kMstQueue};
         // phase 1: find-min-edge with the atomic section
         if (round > 0 && x0 < 0) x0 = dominant<B>(p, sm);
         find_min_edges<B>(p, sm, tm, in, cnt_in, wq, &ctrl->cnt[(round + 1) % 3], out, scanned,
                           x0 < 0 ? -2 : p.comp[x0]);
-        block_drain<B, kMstQueue>(wq, sm.fill, &sm.base, &ctrl->cnt[(round + 1) % 3], out, n, ctrl);
+        block_drain<B>(wq, sm.fill, &sm.base, &ctrl->cnt[(round + 1) % 3], out, n, ctrl);
         if (!(ok = grid_barrier(ctrl, bs, &sm.flag, nullptr, tm))) break;
         // phase 2: hook every root with a candidate, emit its edge through the
         // wavefront's LDS queue (one atomic per wavefront and step on the one
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(B) void mst_kernel(MstParams p) {
             }
             wq.push(emit, e, fcnt, p.forest, n, ctrl);
         }
-        block_drain<B, kMstQueue>(wq, sm.fill, &sm.base, fcnt, p.forest, n, ctrl);
+        block_drain<B>(wq, sm.fill, &sm.base, fcnt, p.forest, n, ctrl);
         if (!(ok = grid_barrier(ctrl, bs, &sm.flag, nullptr, tm))) break;
         // phase 3: pointer jumping over the hooks, While Any(unfinished): a
         // root follows its hooks for up to kMstChase steps, which ends most

@@ -7,14 +7,27 @@
 namespace irgl {
 
 
-constexpr int kQueueCap = 256;  // LDS staging entries per wavefront
+// LDS staging entries per wavefront.  Every drain reserves its place with an
+// atomic on one word, 11 ns each one after another: an invocation that pushes
+// 1.8M vertices spends 79 us on them with 256 entries per drain (4096^2
+// road-like BFS, 230 us per such invocation), 20 us with 1024.
+// (1024 threads: what fits 64 KiB with the rest of the layout.)
+template <int B>
+constexpr int queue_cap() {
+    return B >= 1024 ? 448 : 1024;
+}
+template <int B>
+constexpr int far_cap() {  // the SSSP far list's
+    return B >= 1024 ? 224 : 256;
+}
+constexpr int kPipeQueueCap = 256;  // a pipe program's nested scheduler, at every size from 64 threads
 constexpr int kHeavyQ = 64;     // LDS staging entries per wavefront for the SSSP heavy list
 constexpr uint32_t kDoAlpha = 14;  // BFS direction choice (irgl_config.do_alpha, do_beta)
 constexpr uint32_t kDoBeta = 96;
 constexpr int kUMax = 4;        // largest edges-per-lane-per-round of any operator
 
 // Shared-memory layout of the frontier kernels for workgroup size B.
-template <int B>
+template <int B, int Q = queue_cap<B>()>
 struct Smem {
     static constexpr int NW = B / kWave;
     int gstart[B];                 // gather tier: first slot of each thread's range (exclusive scan)
@@ -25,8 +38,8 @@ struct Smem {
     int fill[NW];                  // per-wavefront queue fill at the workgroup drain
     union {
         struct {
-            int queue[NW][kQueueCap];      // worklist (near) staging
-            int queue_far[NW][kQueueCap];  // SSSP far-list staging
+            int queue[NW][Q];              // worklist (near) staging
+            int queue_far[NW][far_cap<B>()];  // SSSP far-list staging
             int queue_heavy[NW][kHeavyQ];  // SSSP heavy-list staging (vertices expanded in the current bucket)
         };
         int solo[2][4 * B];  // the two worklists of solo invocations (no queue is in use then)
@@ -43,7 +56,8 @@ struct Smem {
     int hub_h;                     // grid tier: first deferred vertex of this workgroup
     uint32_t tile;                 // next worklist tile of this workgroup
 };
-static_assert(8 * 256 <= 256 / kWave * (2 * kQueueCap + kHeavyQ), "the solo worklists fit the queues' space");
+static_assert(8 * 256 <= 256 / kWave * (kPipeQueueCap + far_cap<256>() + kHeavyQ), "the solo worklists fit the queues' space");
+static_assert(sizeof(Smem<1024>) <= 64 * 1024, "the control kernel admits every workgroup size");
 
 struct Params {
     int32_t n;

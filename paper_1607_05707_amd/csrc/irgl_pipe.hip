@@ -79,8 +79,8 @@ __host__ __device__ inline BodyInfo body_info(int b) {
 // MST_INIT compacts with a workgroup scan laid out for kInitBlock threads.
 template <int B>
 struct QueueSmem {
-    int q_out[B / kWave][kQueueCap];
-    int q_retry[B / kWave][kQueueCap];
+    int q_out[B / kWave][kPipeQueueCap];
+    int q_retry[B / kWave][kPipeQueueCap];
     int fill[B / kWave];
     uint32_t base;
 };
@@ -90,14 +90,14 @@ struct InitSmem {
 };
 template <int B>
 union PipeSmem {
-    Smem<B> nested;
+    Smem<B, kPipeQueueCap> nested;
     QueueSmem<B> queues;
     InitSmem init;
 };
 
 template <int B>
 constexpr size_t body_lds(int b) {
-    return b == IRGL_BODY_BFS_PUSH ? sizeof(Smem<B>)
+    return b == IRGL_BODY_BFS_PUSH ? sizeof(Smem<B, kPipeQueueCap>)
          : b == IRGL_BODY_MST_INIT ? sizeof(InitSmem)
          : body_info(b).uses_wl ? sizeof(QueueSmem<B>) : 0;
 }
@@ -432,30 +432,30 @@ __device__ bool invoke(const Params &p, PipeSmem<B> &sm, int *s_flag, Team tm, B
         }
         const int wid = threadIdx.x / kWave;
         // pushes to `out` land after the items earlier retry rounds left there
-        Pushers pu{{sm.queues.q_out[wid], 0}, {nullptr, 0},
+        Pushers pu{{sm.queues.q_out[wid], 0, kPipeQueueCap}, {nullptr, 0, 0},
                    Sink{&p.cnt->out[i % 3], p.wl[s.out_b] + s.out_base, p.cap - s.out_base, p.ctrl, nullptr},
                    Sink{}, kInf};
-        Pushers pr{{sm.queues.q_retry[wid], 0}, {nullptr, 0},
+        Pushers pr{{sm.queues.q_retry[wid], 0, kPipeQueueCap}, {nullptr, 0, 0},
                    Sink{&p.cnt->retry[i % 3], p.wl[s.retry_b], p.cap, p.ctrl, nullptr}, Sink{}, kInf};
         bool any = false;
         switch (body) {
             case IRGL_BODY_BFS_PUSH:
                 pu.nq.q = sm.nested.queue[wid];
                 bfs_push<B>(p, sm, tm, s, pu);
-                block_drain<B, kQueueCap>(pu.nq, sm.nested.fill, &sm.nested.base, pu.sk.cnt_out, pu.sk.out,
+                block_drain<B>(pu.nq, sm.nested.fill, &sm.nested.base, pu.sk.cnt_out, pu.sk.out,
                                           pu.sk.cap, pu.sk.ctrl);
                 break;
             case IRGL_BODY_BFS_PULL:
                 bfs_pull<B>(p, tm, s, pu);
-                block_drain<B, kQueueCap>(pu.nq, sm.queues.fill, &sm.queues.base, pu.sk.cnt_out, pu.sk.out,
+                block_drain<B>(pu.nq, sm.queues.fill, &sm.queues.base, pu.sk.cnt_out, pu.sk.out,
                                           pu.sk.cap, pu.sk.ctrl);
                 break;
             case IRGL_BODY_MST_INIT: mst_init<B>(p, sm, tm, s); break;
             case IRGL_BODY_MST_FINDMIN:
                 mst_findmin<B>(p, tm, s, pu, pr);
-                block_drain<B, kQueueCap>(pu.nq, sm.queues.fill, &sm.queues.base, pu.sk.cnt_out, pu.sk.out,
+                block_drain<B>(pu.nq, sm.queues.fill, &sm.queues.base, pu.sk.cnt_out, pu.sk.out,
                                           pu.sk.cap, pu.sk.ctrl);
-                block_drain<B, kQueueCap>(pr.nq, sm.queues.fill, &sm.queues.base, pr.sk.cnt_out, pr.sk.out,
+                block_drain<B>(pr.nq, sm.queues.fill, &sm.queues.base, pr.sk.cnt_out, pr.sk.out,
                                           pr.sk.cap, pr.sk.ctrl);
                 break;
             case IRGL_BODY_MST_HOOK: mst_hook<B>(p, tm); break;

@@ -498,7 +498,7 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
     const int tid = threadIdx.x;
     const int wid = tid / kWave;
     Ctrl *ctrl = p.ctrl;
-    Pushers pu{{sm.queue[wid], 0}, {sm.queue_far[wid], 0}, {}, {}, kInf};
+    Pushers pu{{sm.queue[wid], 0, queue_cap<B>()}, {sm.queue_far[wid], 0, far_cap<B>()}, {}, {}, kInf};
     pu.hq.q = sm.queue_heavy[wid];
     // SSSP light/heavy split: expansions relax light ranges and list the
     // vertex for its bucket's heavy pass, which runs in the bucket's transfer
@@ -887,7 +887,7 @@ __global__ __launch_bounds__(B) void level_kernel(Params p) {
     int32_t *out = (it & 1u) ? p.wl0 : p.wl1;
     uint32_t cnt_in = ctrl->cnt[it % 3];
     if (cnt_in > p.cap) cnt_in = p.cap;
-    Pushers pu{{sm.queue[wid], 0}, {sm.queue_far[wid], 0}, Sink{&ctrl->cnt[(it + 1) % 3], out, p.cap, ctrl, nullptr},
+    Pushers pu{{sm.queue[wid], 0, queue_cap<B>()}, {sm.queue_far[wid], 0, far_cap<B>()}, Sink{&ctrl->cnt[(it + 1) % 3], out, p.cap, ctrl, nullptr},
                far_sink(p, p.far_tr), kInf};
     if (blockIdx.x == 0 && tid == 0 && tracing(p, it)) trace_start(p, it, cnt_in);
     if (p.refresh && p.visited) refresh_bitmap(p, whole_grid(), kInf);
@@ -920,7 +920,7 @@ __global__ __launch_bounds__(B) void hub_level_kernel(Params p) {
     hub_counts(ctrl->hub[it % 3], p.hub_cap, nh, nchunks);
     if (nh == 0) return;  // uniform across the grid
     int32_t *out = (it & 1u) ? p.wl0 : p.wl1;
-    Pushers pu{{sm.queue[wid], 0}, {sm.queue_far[wid], 0}, Sink{&ctrl->cnt[(it + 1) % 3], out, p.cap, ctrl, nullptr},
+    Pushers pu{{sm.queue[wid], 0, queue_cap<B>()}, {sm.queue_far[wid], 0, far_cap<B>()}, Sink{&ctrl->cnt[(it + 1) % 3], out, p.cap, ctrl, nullptr},
                far_sink(p, p.far_tr), kInf};
     const Op op = make_op<Op>(p, it, p.thresh);
     expand_hubs<B, Op>(nh, nchunks, p.hub_v, p.hub_base, p.row_ptr, p.col, op, sm, pu, whole_grid());
@@ -937,7 +937,7 @@ __global__ __launch_bounds__(B) void transfer_kernel(Params p, uint32_t far_n, u
     const uint32_t it = p.it;
     const uint32_t tr = p.far_tr;
     int32_t *out = (it & 1u) ? p.wl0 : p.wl1;
-    Pushers pu{{sm.queue[wid], 0}, {sm.queue_far[wid], 0}, Sink{&ctrl->cnt[(it + 1) % 3], out, p.cap, ctrl, nullptr},
+    Pushers pu{{sm.queue[wid], 0, queue_cap<B>()}, {sm.queue_far[wid], 0, far_cap<B>()}, Sink{&ctrl->cnt[(it + 1) % 3], out, p.cap, ctrl, nullptr},
                far_sink(p, tr + 1), kInf};
     if (blockIdx.x == 0 && threadIdx.x == 0 && tracing(p, it)) {
         trace_start(p, it, 0u);
@@ -972,7 +972,7 @@ template <int B>
 __global__ __launch_bounds__(B) void sssp_parent_kernel(Params p) {
     __shared__ Smem<B> sm;
     const int wid = threadIdx.x / kWave;
-    Pushers pu{{sm.queue[wid], 0}, {sm.queue_far[wid], 0}, Sink{nullptr, nullptr, 0u, p.ctrl, nullptr},
+    Pushers pu{{sm.queue[wid], 0, queue_cap<B>()}, {sm.queue_far[wid], 0, far_cap<B>()}, Sink{nullptr, nullptr, 0u, p.ctrl, nullptr},
                Sink{nullptr, nullptr, 0u, p.ctrl, nullptr}, kInf};
     unsigned long long edges = 0;
     const SsspParentOp op{p.val, p.w, p.parent, p.src, p.perm};

@@ -141,7 +141,7 @@ template <int B, class Op>
 __device__ __forceinline__ LoopResult run_topology(const Params &p, Smem<B> &sm, Team tm, BarrierState &bs) {
     const int wid = threadIdx.x / kWave;
     Ctrl *ctrl = p.ctrl;
-    Pushers pu{{sm.queue[wid], 0}, {sm.queue_far[wid], 0}, Sink{nullptr, nullptr, 0u, ctrl, nullptr},
+    Pushers pu{{sm.queue[wid], 0, queue_cap<B>()}, {sm.queue_far[wid], 0, far_cap<B>()}, Sink{nullptr, nullptr, 0u, ctrl, nullptr},
                Sink{nullptr, nullptr, 0u, ctrl, nullptr}, kInf};
     LoopResult r{0u, 0ull, 0ull, 0u, 0ull, 0u};
     const bool lead = tm.id == 0 && threadIdx.x == 0;
