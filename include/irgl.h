@@ -166,7 +166,10 @@ typedef struct irgl_config {
                              invocation to bottom-up (every unvisited vertex looks
                              for a neighbour in the frontier, first hit wins) when
                              the frontier's edges exceed the unexplored edges /
-                             do_alpha; default 14; IRGL_DO_OFF = always top-down */
+                             do_alpha; default: 10, or of graphs whose largest
+                             degree is at most 16 times the mean 4, and
+                             IRGL_DO_OFF where that mean is below 4.5;
+                             IRGL_DO_OFF = always top-down */
     uint32_t do_beta;     /* ... and back to top-down when the frontier holds fewer
                              than n / do_beta vertices (default 96) */
     uint32_t delta;       /* SSSP: near/far threshold step.  Distances below the

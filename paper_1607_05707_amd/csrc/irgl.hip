@@ -143,6 +143,7 @@ uint32_t delta_rule(const irgl_graph_s *g, bool partitioned);
 // The scale-free branch of the rule (mean degree at least kDeltaMinDegree,
 // largest out-degree above kSkew times the mean), from the validation pass.
 bool scale_free(const irgl_graph_s *g);
+uint32_t do_alpha_rule(const irgl_graph_s *g);
 // Far-list divisor of the bucketing's early end on split scale-free graphs:
 // it ends once the far list holds fewer than (items popped so far) /
 // kTailDiv vertices.  Re-derived once an expansion without a threshold
@@ -359,7 +360,7 @@ irgl_status resolve(const irgl_graph_s *g, int kind, const irgl_config *c, Cfg *
                                     : (kind == IRGL_KIND_SSSP ? IRGL_BITMAP_NEVER : default_t_bitmap(g->n, g->m));
     // direction optimization needs in-edges = out-edges and the outlined loop
     const bool sym = (g->flags & IRGL_SYMMETRIC) != 0;
-    r.do_alpha = (c && c->do_alpha) ? c->do_alpha : kDoAlpha;
+    r.do_alpha = (c && c->do_alpha) ? c->do_alpha : do_alpha_rule(g);
     // back to top-down below n / 96 frontier vertices (16 sources, us per
     // query at 24 / 48 / 96 / 192: RMAT-20 234 / 230 / 229 / 229, RMAT-21
     // 310 / 308 / 308 / 305, RMAT-22 366 / 363 / 360 / 360, RMAT-23 565 /
@@ -959,7 +960,8 @@ int64_t task_cost(const irgl_task &t) {
 void fill_desc(TaskDesc &d, const irgl_task &t, Stats *stats, uint32_t delta_override, bool gang = false) {
     std::memset(&d, 0, sizeof(d));
     d.gang = gang ? 1u : 0u;
-    d.pull = t.kind == IRGL_KIND_BFS && (t.g->flags & IRGL_SYMMETRIC) ? 1u : 0u;
+    d.do_alpha = t.kind == IRGL_KIND_BFS && (t.g->flags & IRGL_SYMMETRIC) ? do_alpha_rule(t.g) : 0u;
+    if (d.do_alpha == IRGL_DO_OFF) d.do_alpha = 0u;
     d.row_ptr = t.g->orig_row_ptr;
     d.col = t.g->orig_col;
     d.w = t.g->orig_w;
@@ -1025,6 +1027,31 @@ bool scale_free(const irgl_graph_s *g) {
     if (!g->weight_sum || g->m <= 0 || g->n <= 0) return false;
     const double mean_deg = static_cast<double>(g->m) / static_cast<double>(g->n);
     return mean_deg >= kDeltaMinDegree && static_cast<double>(g->max_degree) > kSkew * mean_deg;
+}
+
+// Default direction choice of symmetric graphs: the alpha of a level's switch
+// to bottom-up, by how much of a row an open vertex scans before it meets the
+// frontier.  us per query at alpha 4 / 6 / 8 / 10 / 14 / off:
+//   skewed: R-MAT 16 x 16 112 / 111 / 112 / 111 / 121 / 237, 20 x 16 298 / 299
+//   / 234 / 207 / 208 / 791, 21 x 8 355 / 298 / 298 / 297 / 352 / 872, 22 x 16
+//   604 / 385 / 383 / 386 / 384 / 1481, 19 x 2 (mean degree 3.9) 222 / 170 /
+//   170 / - / 170 / 308;
+//   even rows: uniform 600,000 x 5 342 / - / 418 / - / 418 / 390, x 6 319 / - /
+//   342 / - / 430, x 7 321 / 349 / - / - / 424, 4M x 9 584 / 608 / 728 / 730 /
+//   767 / 789, 600,000 x 12 287 at all, 1M x 24 264 at all but off (437);
+//   even rows below a mean degree of 4.5, where most of a row is scanned in
+//   vain and the degree sum of each push (a gather of its row bounds) costs
+//   more than bottom-up saves: uniform 600,000 x 4 258 / - / - / - / 284 / 246,
+//   road-like 512^2 - / 482 / 434 (14 / off), 2048^2 1401 / 1040, 4096^2 3210 /
+//   2608, grid 1500^2 30768 / 20374.
+// An unvalidated upload's largest degree is unknown: as skewed.
+uint32_t do_alpha_rule(const irgl_graph_s *g) {
+    constexpr double kEvenMinDegree = 4.5;
+    constexpr uint32_t kEvenAlpha = 4;
+    if (!g->max_degree || g->n <= 0) return kDoAlpha;
+    const double mean_deg = static_cast<double>(g->m) / static_cast<double>(g->n);
+    if (static_cast<double>(g->max_degree) > kSkew * mean_deg) return kDoAlpha;
+    return mean_deg < kEvenMinDegree ? IRGL_DO_OFF : kEvenAlpha;
 }
 
 // The mean weight is known when the upload validated the graph.

@@ -30,7 +30,7 @@ struct TaskDesc {
     uint32_t max_iter;
     uint32_t t_bitmap;   // bitmap refresh point (new items since the last refresh)
     uint32_t gang;       // server: run on the whole grid (all teams together)
-    uint32_t pull;       // BFS on a symmetric graph: bottom-up invocations where they scan less
+    uint32_t do_alpha;   // BFS on a symmetric graph: the switch to bottom-up (0: top-down only)
 };
 
 struct BatchParams {
@@ -106,9 +106,9 @@ __device__ __forceinline__ Params task_params(const BatchParams &bp, const TaskD
     // Bottom-up invocations as in a single query (16 teams on 16 BFS tasks on
     // RMAT-18, 7.6M entries each: 1.4 ms of a team's time per task top-down)
     const uint32_t bm = ((static_cast<uint32_t>(t.n) + 31u) / 32u * 4u + 255u) & ~255u;
-    p.frontier = t.pull ? reinterpret_cast<uint32_t *>(base + bp.off_visited + bm) : nullptr;
-    p.frontier2 = t.pull ? reinterpret_cast<uint32_t *>(base + bp.off_visited + 2 * bm) : nullptr;
-    p.do_alpha = kDoAlpha;
+    p.frontier = t.do_alpha ? reinterpret_cast<uint32_t *>(base + bp.off_visited + bm) : nullptr;
+    p.frontier2 = t.do_alpha ? reinterpret_cast<uint32_t *>(base + bp.off_visited + 2 * bm) : nullptr;
+    p.do_alpha = t.do_alpha;
     p.do_beta = kDoBeta;
     p.m = m;
     p.reduce_all = 0;

@@ -22,7 +22,7 @@ constexpr int far_cap() {  // the SSSP far list's
 }
 constexpr int kPipeQueueCap = 256;  // a pipe program's nested scheduler, at every size from 64 threads
 constexpr int kHeavyQ = 64;     // LDS staging entries per wavefront for the SSSP heavy list
-constexpr uint32_t kDoAlpha = 14;  // BFS direction choice (irgl_config.do_alpha, do_beta)
+constexpr uint32_t kDoAlpha = 10;  // BFS direction choice (irgl_config.do_alpha, do_beta); see do_alpha_rule
 constexpr uint32_t kDoBeta = 96;
 constexpr int kUMax = 4;        // largest edges-per-lane-per-round of any operator
 
