@@ -159,7 +159,8 @@ typedef struct irgl_config {
                              threshold) lets relaxations skip them with an L2 bit
                              test.  It is rebuilt by a full scan once this many
                              items were popped since the last rebuild (BFS default
-                             n^2 / 2m); IRGL_BITMAP_NEVER disables it (the SSSP
+                             n^2 / 2m; BFS also waits for a frontier of at least
+                             half of those items); IRGL_BITMAP_NEVER disables it (the SSSP
                              default) */
     uint32_t trace_len;   /* entries of `trace` */
     uint32_t do_alpha;    /* BFS on a symmetric graph (IRGL_SYMMETRIC): switch an

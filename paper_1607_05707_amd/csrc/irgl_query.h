@@ -531,6 +531,8 @@ struct LoopResult {
     uint32_t pulls;             // SSSP heavy passes run as a pull (uniform)
 };
 
+constexpr unsigned long long kRefreshShare = 2;
+
 template <int B, class Op, bool kSolo>
 __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, Team tm, BarrierState &bs) {
     const int tid = threadIdx.x;
@@ -561,6 +563,7 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
     // popped items when the bitmap was last refreshed: refresh again once the
     // newly reached vertices carry enough edges to repay a full scan
     unsigned long long refreshed = 0;
+    bool filter = false;  // the bitmap has been refreshed: BFS expansions probe it
     unsigned long long hdone = 0;  // heavy edges of the buckets drained so far
 
     // Solo runs (irgl_solo.h) need the plain worklists: not on a split graph,
@@ -789,6 +792,7 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
             fr_next = fr_t;
             bitmaps_current = true;
             refreshed = r.items;  // the visited bitmap is exact again
+            filter = true;
             drain_all<B, Op>(pu, sm);
             add_block_total<B>(r.edges - edges_before, &ctrl->bu_scan);
             if (!grid_barrier(ctrl, bs, &sm.flag, p.abort_flag, tm)) break;
@@ -812,11 +816,23 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
             pu.hmin_out = &ctrl->hmin[tr % 3];
             pu.mf_out = &ctrl->mf[(rot + 1) % 3];
             const unsigned long long edges_before = r.edges;
-            if (!Op::kFar && p.visited && r.items - refreshed >= p.t_bitmap) {
+            // A refresh repays where the frontier is at least 1 / kRefreshShare of
+            // what was reached since the last one: the vertices that a long
+            // narrow traversal meets again are those of its last levels, which
+            // no refresh has seen.  us per BFS with every refresh / share 16 /
+            // share 2 / no bitmap: road-like 4096^2 2607 / 2594 / 2315 / 2316,
+            // 1000^2 611 / 605 / 576 / 568; uniform 4M x 4 698 / 701 / 694 /
+            // 742; directed 1.5M x 11 427 / 426 / 424 / 448.
+            if (!Op::kFar && p.visited && r.items - refreshed >= p.t_bitmap &&
+                cnt_in >= (r.items - refreshed) / kRefreshShare) {
                 refresh_bitmap(p, tm, kInf);  // BFS: visited = labelled
                 refreshed = r.items;
+                filter = true;
             }
-            const Op op = make_op<Op>(p, it, thresh, tr, false);
+            Op op = make_op<Op>(p, it, thresh, tr, false);
+            if constexpr (!Op::kFar) {
+                if (!filter) op.visited = nullptr;  // all clear: nothing to probe for
+            }
             const bool tr_on = tracing(p, it);
             unsigned long long busy_a = tr_on ? wall_clock64() : 0ull, busy_b = 0;
             expand<B, Op>(in, cnt_in, static_cast<uint32_t>(p.n), p.row_ptr, p.col, op, sm, pu, p.t_wave,

@@ -64,3 +64,33 @@ def test_default_direction(irgl, make, top_down):
         b.free()
         for task, ref in zip(tasks, refs):
             np.testing.assert_array_equal(irgl.as_u32_numpy(task.out), ref)
+
+
+@pytest.mark.parametrize("path,width", [(3, 700), (900, 5000), (2100, 2100)])
+def test_refreshes_of_the_visited_bitmap(irgl, path, width):
+    """A path, then a fan of `width` vertices joined to one another, then a path."""
+    a = list(range(path)) + [path] * width
+    b = list(range(1, path + 1)) + [path + 1 + i for i in range(width)]
+    rng = np.random.default_rng(path)
+    a += [path + 1 + i for i in range(width)] * 2
+    b += (path + 1 + rng.integers(0, width, 2 * width)).tolist()
+    a += [path + width + i for i in range(path)]
+    b += [path + 1 + width + i for i in range(path)]
+    n = 2 * path + 1 + width
+    g = gg.from_edges(n, a, b, [1] * len(a))
+    rp, col, _ = g.numpy()
+    ref, whole = oracle.bfs(rp, col, 0)[0], len(a)
+    for symmetric in (False, True):
+        if symmetric:
+            g = gg.from_edges(n, a + b, b + a, [1] * (2 * len(a)))
+            g.symmetric = True
+            rp, col, _ = g.numpy()
+            ref, whole = oracle.bfs(rp, col, 0)[0], 2 * len(a)
+        hg = irgl.upload(g.to("cuda"))
+        for t_bitmap in (0, 1, 64, width, 0xFFFFFFFF):
+            for cfg in ({"grid": 4}, {"grid": 1, "block": 256}, {}):
+                cfg = dict(cfg, t_bitmap=t_bitmap, do_alpha=0xFFFFFFFF)
+                print(f"[case] {path} {width} symmetric={symmetric} {cfg}", flush=True)
+                out, _, st = irgl.query(hg, BFS, 0, with_parent=True, cfg=cfg)
+                np.testing.assert_array_equal(irgl.as_u32_numpy(out), ref)
+                assert st["edges"] == whole
