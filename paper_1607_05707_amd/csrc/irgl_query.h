@@ -401,34 +401,8 @@ constexpr int kPullMaxRange = 1024;
 
 constexpr int kPullBatch = 8;
 
-// One bit per vertex listed in bucket `bucket`, into `listed`.  The heavy
-// pass probes it once per entry, at random: n / 8 bytes stay in an XCD's L2,
-// and the hubs' words, first in a relabelled graph, in the CUs' caches, where
-// the bucket stamps themselves (4 n bytes) reach past both.
-__device__ __forceinline__ void build_listed(const Params &p, uint32_t bucket, Team tm, uint32_t *listed) {
-    const uint32_t n = static_cast<uint32_t>(p.n);
-    const uint32_t step = blockDim.x * kPullV;
-    const int lane = lane_id();
-    for (uint32_t base = tm.id * step; base < n; base += tm.size * step) {
-        uint32_t hs[kPullV];
-#pragma unroll
-        for (int j = 0; j < kPullV; ++j) {
-            const uint32_t v = base + j * blockDim.x + threadIdx.x;
-            hs[j] = v < n ? p.hstamp[v] : kInf;
-        }
-        phase(hs);
-#pragma unroll
-        for (int j = 0; j < kPullV; ++j) {
-            const uint32_t v = base + j * blockDim.x + threadIdx.x;
-            const unsigned long long m = __ballot(v < n && hs[j] == bucket);
-            if (lane == 0 && v < n) listed[v >> 5] = static_cast<uint32_t>(m);
-            if (lane == 32 && v < n) listed[v >> 5] = static_cast<uint32_t>(m >> 32);
-        }
-    }
-}
-
 template <int B, class Op>
-__device__ __forceinline__ void pull_heavy(const Params &p, const Op &hop, uint32_t lo, const uint32_t *listed, Team tm,
+__device__ __forceinline__ void pull_heavy(const Params &p, const Op &hop, uint32_t lo, uint32_t bucket, Team tm,
                                            Pushers &pu, unsigned long long &scanned, uint32_t *big) {
     const uint32_t n = static_cast<uint32_t>(p.n);
     bool saw_big = false;
@@ -455,14 +429,12 @@ __device__ __forceinline__ void pull_heavy(const Params &p, const Op &hop, uint3
                 r1 = r0;
             }
             unsigned long long best = du;
-            // kPullBatch entries per step: their column loads, then their bit
-            // probes, then the weights and the distances of the listed ones are
-            // in flight together (a long range is otherwise a chain of
-            // dependent loads per entry).  RMAT-22, us per query: 1495 with
-            // stamp probes and a load chain per listed entry, 1455 now.
+            // kPullBatch entries per step: their column loads, then their
+            // bucket-stamp probes, are in flight together (a long range is
+            // otherwise one dependent pair of loads per entry)
             for (int x0 = r0; x0 < r1; x0 += kPullBatch) {
                 int vb[kPullBatch], va[4], vc[4];
-                uint32_t hb[kPullBatch], dvb[kPullBatch];
+                uint32_t hb[kPullBatch];
                 load4(p.col, x0, p.m, r1 - 1, va);
                 load4(p.col, min(x0 + 4, r1 - 1), p.m, r1 - 1, vc);
 #pragma unroll
@@ -472,31 +444,21 @@ __device__ __forceinline__ void pull_heavy(const Params &p, const Op &hop, uint3
                 }
                 phase(vb);
 #pragma unroll
-                for (int k = 0; k < kPullBatch; ++k) hb[k] = listed[static_cast<uint32_t>(vb[k]) >> 5];
+                for (int k = 0; k < kPullBatch; ++k) hb[k] = p.hstamp[vb[k]];
                 phase(hb);
-                bool any = false;
 #pragma unroll
                 for (int k = 0; k < kPullBatch; ++k) {
-                    hb[k] = x0 + k < r1 ? hb[k] >> (vb[k] & 31) & 1u : 0u;
-                    any |= hb[k] != 0u;
-                }
-                if (!any) continue;
-                int wa[4], wc[4];
-                load4(reinterpret_cast<const int32_t *>(p.w), x0, p.m, r1 - 1, wa);
-                load4(reinterpret_cast<const int32_t *>(p.w), min(x0 + 4, r1 - 1), p.m, r1 - 1, wc);
-#pragma unroll
-                for (int k = 0; k < kPullBatch; ++k) dvb[k] = p.val[hb[k] ? vb[k] : static_cast<int>(u)];
-                phase(dvb);
-#pragma unroll
-                for (int k = 0; k < kPullBatch; ++k) {
-                    const uint32_t wv = static_cast<uint32_t>(k < 4 ? wa[k & 3] : wc[k & 3]);
+                    if (x0 + k >= r1 || hb[k] != bucket) continue;
+                    const int v = vb[k];
+                    const uint32_t dvv = p.val[v];
+                    const uint32_t wv = p.w[x0 + k];
                     const unsigned long long c =
-                        static_cast<unsigned long long>(dvb[k]) + static_cast<unsigned long long>(wv);
-                    if (hb[k] && c < best) {
+                        static_cast<unsigned long long>(dvv) + static_cast<unsigned long long>(wv);
+                    if (c < best) {
                         best = c;
                         ew[0] = wv;
-                        sv[0] = vb[k];
-                        dv[0] = dvb[k];
+                        sv[0] = v;
+                        dv[0] = dvv;
                         act[0] = true;
                     }
                 }
@@ -708,19 +670,6 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
                 refresh_bitmap(p, tm, thresh);  // every distance below thresh is final
                 refreshed = r.items;
             }
-            // Pull only for a bucket no wider than the step (the smallest
-            // expanded distance plus the step reaches the drained threshold):
-            // then the vertices it scans are those beyond the threshold.
-            const uint32_t hm = load_agent(&ctrl->hmin[tr % 3]);
-            const uint32_t lo = hm >= kInf - p.delta ? kInf : hm + p.delta;
-            // Its bitmap takes the place of the worklist just used up, where that
-            // has the room.
-            const bool pull_h = nheavy > 0 && p.cap >= (static_cast<uint32_t>(p.n) + 31u) / 32u &&
-                                p.pull_heavy_div && lo >= thresh &&
-                                hs * p.pull_heavy_div >= static_cast<unsigned long long>(p.n) &&
-                                (p.pull_open_div == 0 || hs * p.pull_open_div >= open);
-            uint32_t *const listed = reinterpret_cast<uint32_t *>(const_cast<int32_t *>(in));
-            if (pull_h) build_listed(p, tr, tm, listed);
             pu.skf = far_sink(p, tr + 1);
             pu.skh = Sink{};
             pu.hsum_out = nullptr;
@@ -735,10 +684,17 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
             // seen from the other end of a symmetric graph).
             const unsigned long long edges_before = r.edges;
             const Op hop = make_op<Op>(p, it, t_new, tr, true);
+            // Pull only for a bucket no wider than the step (the smallest
+            // expanded distance plus the step reaches the drained threshold):
+            // then the vertices it scans are those beyond the threshold.
+            const uint32_t hm = load_agent(&ctrl->hmin[tr % 3]);
+            const uint32_t lo = hm >= kInf - p.delta ? kInf : hm + p.delta;
+            bool pull_h = nheavy > 0 && p.pull_heavy_div && lo >= thresh &&
+                          hs * p.pull_heavy_div >= static_cast<unsigned long long>(p.n) &&
+                          (p.pull_open_div == 0 || hs * p.pull_open_div >= open);
             bool pulled = false;
             if (pull_h) {
-                if (!grid_barrier(ctrl, bs, &sm.flag, p.abort_flag, tm)) break;
-                if constexpr (Op::kFar) pull_heavy<B, Op>(p, hop, lo, listed, tm, pu, r.edges, &ctrl->hbig[rot % 3]);
+                if constexpr (Op::kFar) pull_heavy<B, Op>(p, hop, lo, tr, tm, pu, r.edges, &ctrl->hbig[rot % 3]);
                 drain_all<B, Op>(pu, sm);
                 if (!grid_barrier(ctrl, bs, &sm.flag, p.abort_flag, tm)) break;
                 // an unsettled vertex with a long heavy range was left out: the
