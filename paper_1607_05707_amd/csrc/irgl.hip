@@ -263,9 +263,6 @@ void resolve_tiers(int block, int t_wave, int t_block, int t_grid, int *ow, int 
     *og = g;
 }
 
-// Default workgroup size per kind, from sweeps over road and RMAT graphs:
-// BFS invocations are short, and 1024-thread workgroups cut the barrier
-// arrivals per invocation fourfold; SSSP's longer invocations do best at 512.
 // Default launch shape of outlined single queries (block and grid both left
 // at 0).  More workgroups relax more edges at a time but cost every barrier:
 // each drops its caches at the end, one after another on an XCD's L2 (3.6 us
