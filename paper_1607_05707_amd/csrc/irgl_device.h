@@ -37,8 +37,9 @@ struct alignas(128) Ctrl {
     uint32_t far_min[3];
     // rotating BFS sums of out-degrees of the next frontier (direction choice)
     unsigned long long mf[3];
-    // BFS: edges scanned by bottom-up invocations so far (grows, never reset)
-    unsigned long long bu_scan;
+    // spanning forest: edges emitted so far
+    uint32_t forest;
+    uint32_t pad0b;
     // rotating worklist-tile counters (tiles taken beyond each workgroup's first)
     uint32_t tile[3];
     // rotating ReduceAndReturn words of the topology-driven loop (one per invocation)
@@ -82,7 +83,7 @@ struct alignas(128) Ctrl {
     uint32_t hbig[3];
     uint32_t pulls;  // SSSP heavy passes run as a pull
     uint32_t pad4[6];
-    // line 14: loop state after a solo run, rotating like the worklist counters
+    // line 13: loop state after a solo run, rotating like the worklist counters
     struct Solo {
         uint32_t it;      // invocations so far
         uint32_t tr;      // SSSP threshold raises so far
@@ -91,7 +92,12 @@ struct alignas(128) Ctrl {
         unsigned long long items;   // items popped so far
         unsigned long long m_seen;  // out-degree sum of all worklists so far
     } solo[3];
-    uint32_t pad5[8];
+    // rotating (per invocation) BFS: edges a bottom-up invocation scanned.  Read
+    // after its last barrier, while others may already be adding the next
+    // one's, so invocation `it` uses bu_scan[it % 3] and clears
+    // bu_scan[(it + 1) % 3], which was last read two invocations ago.
+    unsigned long long bu_scan[3];
+    uint32_t pad5[2];
 };
 static_assert(sizeof(Ctrl) == 14 * 128, "control block layout");
 

@@ -97,9 +97,8 @@ struct MstParams {
 };
 
 // The launch reuses control-block counters: cnt[] for the rotating worklist
-// counts, red[] for the pointer-jumping reduction, bu_scan for the number of
+// counts, red[] for the pointer-jumping reduction, forest for the number of
 // emitted forest edges.
-__device__ __forceinline__ uint32_t *forest_count(Ctrl *c) { return reinterpret_cast<uint32_t *>(&c->bu_scan); }
 
 template <int B>
 struct MstSmem {
@@ -498,7 +497,7 @@ __global__ __launch_bounds__(B) void mst_kernel(MstParams p) {
     // same vertex names it in every round, so its vertices may leave the
     // worklist for good.
     int x0 = -1;
-    uint32_t *const fcnt = forest_count(ctrl);
+    uint32_t *const fcnt = &ctrl->forest;
     bool ok = true;
     for (;; ++round) {
         const uint32_t cnt_in = round == 0 ? n : min(load_agent(&ctrl->cnt[round % 3]), n);
@@ -689,7 +688,7 @@ __global__ void mst_init_kernel(MstParams p, unsigned long long m) {
             c->cnt[k] = 0;
             c->red[k] = 0;
         }
-        c->bu_scan = 0;
+        c->forest = 0;
         reset_barrier_words(c);
         c->error = 0;
         c->fatal = 0;

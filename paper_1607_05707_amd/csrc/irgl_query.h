@@ -52,6 +52,7 @@ __device__ __forceinline__ void init_control(const Params &p, bool reset_barrier
             c->hsum[k] = 0;
             c->hmin[k] = kInf;
             c->hbig[k] = 0;
+            c->bu_scan[k] = 0;
         }
         if (reset_barrier) reset_barrier_words(c);
         c->error = 0;
@@ -66,7 +67,6 @@ __device__ __forceinline__ void init_control(const Params &p, bool reset_barrier
         c->mf[0] = static_cast<unsigned long long>(p.row_ptr[p.src + 1] - p.row_ptr[p.src]);
         c->mf[1] = 0;
         c->mf[2] = 0;
-        c->bu_scan = 0;
         p.wl0[0] = p.src;
 }
 
@@ -514,7 +514,6 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
     uint32_t *fr_cur = p.frontier, *fr_next = p.frontier2;
     unsigned long long m_seen = 0;  // out-degree sum of all worklists so far
     unsigned long long m_f = 0;     // out-degree sum of this invocation's worklist
-    unsigned long long bu_seen = 0; // ctrl->bu_scan after the last bottom-up invocation
     if (can_pull) pu.deg_rp = p.row_ptr;
     const int32_t *in = p.wl0;
     int32_t *out = p.wl1;
@@ -562,6 +561,7 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
             __hip_atomic_store(&ctrl->mf[(rot + 2) % 3], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // read inside invocation rot after a barrier of it: clear the next one's
             store_agent(&ctrl->hbig[(rot + 1) % 3], 0u);
+            __hip_atomic_store(&ctrl->bu_scan[(rot + 1) % 3], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         if constexpr (kSolo) {
             if (solo) {
@@ -750,19 +750,16 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
             refreshed = r.items;  // the visited bitmap is exact again
             filter = true;
             drain_all<B, Op>(pu, sm);
-            add_block_total<B>(r.edges - edges_before, &ctrl->bu_scan);
+            add_block_total<B>(r.edges - edges_before, &ctrl->bu_scan[rot % 3]);
             if (!grid_barrier(ctrl, bs, &sm.flag, p.abort_flag, tm)) break;
             // uniform: a bottom-up invocation that scanned more than twice the
             // edges the top-down one would have (a high-diameter graph, where
             // unvisited vertices rarely touch the frontier) ends bottom-up for
             // the query
-            const unsigned long long bu_now =
-                __hip_atomic_load(&ctrl->bu_scan, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (bu_now - bu_seen > 2 * m_f) {
+            if (__hip_atomic_load(&ctrl->bu_scan[rot % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 2 * m_f) {
                 can_pull = false;
                 pull = false;
             }
-            bu_seen = bu_now;
             if (tracing(p, it)) trace_level(p, it, r.edges - edges_before, hub_ctr, tm, pu);
         } else {
             bitmaps_current = false;  // top-down labels are not in the bitmaps
