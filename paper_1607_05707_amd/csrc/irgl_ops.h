@@ -45,9 +45,11 @@ struct Smem {
         int solo[2][4 * B];  // the two worklists of solo invocations (no queue is in use then)
     };
     uint32_t solo_cnt[3];          // solo: rotating worklist counters
+    uint32_t solo_steps;           // solo: invocations the run may take
     uint32_t solo_far[2];          // solo: entries of the two far lists ...
     uint32_t solo_fmin[2];         // ... and lower bounds of their distances
     unsigned long long solo_sum;   // solo: out-degree sum of the worklist left at the end
+    unsigned long long solo_until; // solo: when the run's time is up
     int owner;                     // workgroup-tier vertex owner
     int big_r0, big_r1, big_v;
     uint32_t big_val;

@@ -576,6 +576,7 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
                     const uint32_t left = solo_run<B, Op>(
                         in, cnt_in, out, p.cap, static_cast<uint32_t>(p.n), p.row_ptr, p.col, p.val, p.expd, p.far_flag,
                         p.stamp, p.far0, p.far1, p.far_cap, p.delta, p.max_iter, ctrl, sm, st, r.edges,
+                        tm.size == 1 ? ~0ull : wall_clock64() + bs.wd_ticks / kSoloShare,
                         [&](uint32_t i, uint32_t th, uint32_t t) {
                             Op op = make_op<Op>(p, i, th, t, false);
                             if constexpr (!Op::kFar) op.visited = nullptr;  // the claim alone: one round trip less

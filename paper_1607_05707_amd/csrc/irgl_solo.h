@@ -17,14 +17,20 @@ namespace irgl {
 // A solo run pops worklists of at most kSoloItems vertices (kSoloPer per
 // thread of its wavefronts, looked up together; fewer in a workgroup with
 // fewer wavefronts) with at most kSoloEdges edges, and leaves larger ones to
-// the team: one compute unit looks up about one scattered address per clock.  It also ends after kSoloSteps
-// invocations, so that the waiting workgroups pass a barrier (watchdog, host
-// abort flag) at least once a few milliseconds.
+// the team: one compute unit looks up about one scattered address per clock.
+// It also ends after kSoloSteps invocations, so that the host abort flag is
+// seen every few milliseconds, and once a share of the watchdog's bound has
+// passed: the other workgroups wait at one barrier all the while.  The clock
+// is read every kSoloClock invocations (a full one takes about 10 us, so a
+// bound of 1 ms is kept with half of it to spare; one of 512 invocations on
+// 1000 items each took longer).
 constexpr int kSoloWaves = 8;
 constexpr int kSoloPer = 2;
 constexpr uint32_t kSoloItems = kSoloWaves * kWave * kSoloPer;
 constexpr uint32_t kSoloEdges = 4096;
 constexpr uint32_t kSoloSteps = 512;
+constexpr uint32_t kSoloClock = 8;
+constexpr unsigned long long kSoloShare = 4;
 // Far lists of at most this many entries are transferred solo.
 constexpr uint32_t kSoloFar = 2048;
 // Rows of at most this many edges are walked by the thread that popped them;
@@ -122,7 +128,8 @@ struct SoloState {
 // `out`.  All threads of the workgroup call it.  Returns the items left;
 // `edges` grows by this thread's share of the scanned edges.  trace_begin(it,
 // items) says whether an invocation is traced, trace_end(it, edges scanned by
-// this thread so far, busy ticks, pushers) records it.
+// this thread so far, busy ticks, pushers) records it.  `until`: the
+// wall-clock tick that ends the run.
 template <int B, class Op, class MakeOp, class Begin, class End>
 __device__ __forceinline__ uint32_t solo_run(const int32_t *in, uint32_t cnt_in, int32_t *out, uint32_t cap,
                                              uint32_t n, const int32_t *__restrict__ row_ptr,
@@ -130,7 +137,8 @@ __device__ __forceinline__ uint32_t solo_run(const int32_t *in, uint32_t cnt_in,
                                              uint32_t *far_flag, uint32_t *stamp, int32_t *far0, int32_t *far1,
                                              uint32_t far_cap, uint32_t delta, uint32_t max_iter, Ctrl *ctrl,
                                              Smem<B> &sm, SoloState &st, unsigned long long &edges,
-                                             MakeOp make, Begin trace_begin, End trace_end) {
+                                             unsigned long long until, MakeOp make, Begin trace_begin,
+                                             End trace_end) {
     constexpr int kU = 4;
     constexpr int J = kSoloPer;
     constexpr int kWaves = B / kWave < kSoloWaves ? B / kWave : kSoloWaves;
@@ -147,6 +155,8 @@ __device__ __forceinline__ uint32_t solo_run(const int32_t *in, uint32_t cnt_in,
         sm.solo_cnt[0] = cnt_in;
         sm.solo_cnt[1] = 0u;
         sm.solo_sum = 0ull;
+        sm.solo_steps = kSoloSteps;
+        sm.solo_until = until;
         if (Op::kFar) {
             sm.solo_far[st.tr & 1u] = min(load_agent(&ctrl->far_cnt[st.tr % 3]), far_cap);
             sm.solo_fmin[st.tr & 1u] = load_agent(&ctrl->far_min[st.tr % 3]);
@@ -159,6 +169,7 @@ __device__ __forceinline__ uint32_t solo_run(const int32_t *in, uint32_t cnt_in,
     uint32_t step = 0, cnt = 0;
     __syncthreads();
     for (;; ++step) {
+        const uint32_t most = sm.solo_steps;
         cnt = min(sm.solo_cnt[step % 3], cap);
         uint32_t far_n = 0;
         if (cnt == 0) {
@@ -166,7 +177,7 @@ __device__ __forceinline__ uint32_t solo_run(const int32_t *in, uint32_t cnt_in,
             far_n = min(sm.solo_far[st.tr & 1u], far_cap);
             if (far_n == 0 || far_n > kSoloFar) break;
         }
-        if (cnt > kItems || st.it >= max_iter || step >= kSoloSteps) break;
+        if (cnt > kItems || st.it >= max_iter || step >= most) break;
         if (tid == 0) sm.solo_cnt[(step + 2) % 3] = 0u;
         const bool traced = trace_begin(st.it, cnt);
         const unsigned long long t0 = traced ? wall_clock64() : 0ull;
@@ -312,6 +323,7 @@ __device__ __forceinline__ uint32_t solo_run(const int32_t *in, uint32_t cnt_in,
             pu.fmin = kInf;
         }
         ++st.it;
+        if (step % kSoloClock == kSoloClock - 1 && tid == 0 && wall_clock64() > sm.solo_until) sm.solo_steps = 0u;
         __syncthreads();
     }
     // what is left: the worklist to memory, the counters to the control block
