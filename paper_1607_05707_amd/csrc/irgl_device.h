@@ -114,8 +114,16 @@ struct Stats {
     unsigned long long frontier_edges;
 };
 
+// A constant that takes a register where it is used.  The compiler otherwise
+// prepares the operands of rare stores and atomics at the head of the kernel
+// and holds them to its end: ten registers for the error codes alone.
+__device__ __forceinline__ uint32_t here(uint32_t x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 __device__ __forceinline__ void set_error(Ctrl *c, uint32_t code, bool fatal) {
-    atomicCAS(&c->error, 0u, code);
+    atomicCAS(&c->error, 0u, here(code));
     if (fatal) __hip_atomic_store(&c->fatal, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -127,7 +135,25 @@ __device__ __forceinline__ void store_agent(uint32_t *p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The register cap of a persistent kernel of B threads per workgroup: the
+// fewest waves per SIMD that hold as many whole workgroups per compute unit
+// (four SIMDs) as a cap of W waves per SIMD would.  Where W waves do not
+// divide into whole workgroups (two workgroups of 512 threads fill 4 of 5),
+// the looser cap gives the compiler more registers, hence fewer spills, for
+// the same co-resident grid.
+template <int B, int W>
+constexpr int fit_waves() {
+    constexpr int per_block = B / kWave;
+    constexpr int blocks = (4 * W) / per_block;
+    return blocks <= 0 ? W : (blocks * per_block + 3) / 4;
+}
+static_assert(fit_waves<256, 5>() == 5 && fit_waves<512, 5>() == 4 && fit_waves<1024, 5>() == 4 &&
+                  fit_waves<512, 1>() == 1,
+              "register cap per workgroup size");
+
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
+// This wavefront's index in the workgroup, in a scalar register.
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave); }
 
 // Marks the values of one phase of memory accesses as used here and nowhere
 // earlier.  Without it the compiler moves each load (or atomic) of a phase
@@ -244,7 +270,7 @@ template <int B>
 __device__ __forceinline__ void block_drain(WaveQueue &wq, int *s_fill, uint32_t *s_base,
                                             uint32_t *cnt_out, int *out, uint32_t cap, Ctrl *ctrl) {
     constexpr int NW = B / kWave;
-    const int wid = threadIdx.x / kWave;
+    const int wid = wave_id();
     __syncthreads();
     if (lane_id() == 0) s_fill[wid] = wq.n;
     __syncthreads();
@@ -258,7 +284,8 @@ __device__ __forceinline__ void block_drain(WaveQueue &wq, int *s_fill, uint32_t
     }
     __syncthreads();
     uint32_t base = *s_base;
-    for (int k = 0; k < wid; ++k) base += static_cast<uint32_t>(s_fill[k]);
+#pragma unroll
+    for (int k = 0; k < NW; ++k) base += k < wid ? static_cast<uint32_t>(s_fill[k]) : 0u;
     for (int j = lane_id(); j < wq.n; j += kWave) {
         uint32_t dst = base + static_cast<uint32_t>(j);
         if (dst < cap && dst >= base) out[dst] = wq.q[j];

@@ -475,8 +475,10 @@ __device__ __forceinline__ void find_min_edges(const MstParams &p, MstSmem<B> &s
     }
 }
 
+// Five waves per SIMD: 1280 workgroups of 256 threads, the most an explicit
+// grid may ask for.
 template <int B>
-__global__ __launch_bounds__(B) void mst_kernel(MstParams p) {
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(fit_waves<B, 5>()))) void mst_kernel(MstParams p) {
     __shared__ MstSmem<B> sm;
     const Team tm = whole_grid();
     BarrierState bs = make_barrier_state(p.wd_ticks, p.barrier);

@@ -163,9 +163,13 @@ struct BfsOp {
     static constexpr bool kPush = true;
     static constexpr bool kFar = false;
     // edges per lane per round (memory-level parallelism) and the fewest
-    // waves per SIMD the persistent kernel must fit (1: no register cap)
+    // waves per SIMD the persistent kernel must fit (1: no register cap): at
+    // 4 the co-resident limit, which an explicit grid may ask for, is 512
+    // workgroups of 512 threads or 1024 of 256.  (125 registers, nothing
+    // spilled; 150 before the constants of rare paths were kept out of the
+    // kernel's head, see here() and wave_id(), and half as many workgroups.)
     static constexpr int kU = 4;
-    static constexpr int kMinWaves = 1;
+    static constexpr int kMinWaves = 4;
     uint32_t *level;
     int32_t *parent;
     const uint32_t *visited;  // bitmap: a set bit means "visited" (never a false positive)
@@ -215,22 +219,6 @@ struct BfsOp {
         }
     }
 };
-
-// The register cap of a persistent kernel of B threads per workgroup: the
-// fewest waves per SIMD that hold as many whole workgroups per compute unit
-// (four SIMDs) as a cap of W waves per SIMD would.  Where W waves do not
-// divide into whole workgroups (two workgroups of 512 threads fill 4 of 5),
-// the looser cap gives the compiler more registers, hence fewer spills, for
-// the same co-resident grid.
-template <int B, int W>
-constexpr int fit_waves() {
-    constexpr int per_block = B / kWave;
-    constexpr int blocks = (4 * W) / per_block;
-    return blocks <= 0 ? W : (blocks * per_block + 3) / 4;
-}
-static_assert(fit_waves<256, 5>() == 5 && fit_waves<512, 5>() == 4 && fit_waves<1024, 5>() == 4 &&
-                  fit_waves<512, 1>() == 1,
-              "register cap per workgroup size");
 
 // SSSP relaxation with a near/far split of the worklist (a bucketed,
 // delta-stepping order of the same data-driven loop): an improved vertex

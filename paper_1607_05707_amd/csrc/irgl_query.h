@@ -39,34 +39,35 @@ __device__ __forceinline__ void init_arrays(const Params &p, int with_stamp, Tea
 // counters, which only grow, across the queries it runs.
 __device__ __forceinline__ void init_control(const Params &p, bool reset_barrier) {
         Ctrl *c = p.ctrl;
-        c->cnt[0] = 1;
-        c->cnt[1] = 0;
-        c->cnt[2] = 0;
+        const uint32_t zero = here(0u), inf = here(kInf);
+        c->cnt[0] = zero + 1u;
+        c->cnt[1] = zero;
+        c->cnt[2] = zero;
         for (int k = 0; k < 3; ++k) {
-            c->tile[k] = 0;
-            c->red[k] = 0;
-            c->hub[k] = 0;
-            c->far_cnt[k] = 0;
-            c->far_min[k] = kInf;
-            c->hcnt[k] = 0;
-            c->hsum[k] = 0;
-            c->hmin[k] = kInf;
-            c->hbig[k] = 0;
-            c->bu_scan[k] = 0;
+            c->tile[k] = zero;
+            c->red[k] = zero;
+            c->hub[k] = zero;
+            c->far_cnt[k] = zero;
+            c->far_min[k] = inf;
+            c->hcnt[k] = zero;
+            c->hsum[k] = zero;
+            c->hmin[k] = inf;
+            c->hbig[k] = zero;
+            c->bu_scan[k] = zero;
         }
         if (reset_barrier) reset_barrier_words(c);
-        c->error = 0;
-        c->fatal = 0;
-        c->done = 0;
-        c->iterations = 0;
-        c->max_frontier = 0;
-        c->items = 0;
-        c->edges = 0;
-        c->fedges = 0;
-        c->pulls = 0;
+        c->error = zero;
+        c->fatal = zero;
+        c->done = zero;
+        c->iterations = zero;
+        c->max_frontier = zero;
+        c->items = zero;
+        c->edges = zero;
+        c->fedges = zero;
+        c->pulls = zero;
         c->mf[0] = static_cast<unsigned long long>(p.row_ptr[p.src + 1] - p.row_ptr[p.src]);
-        c->mf[1] = 0;
-        c->mf[2] = 0;
+        c->mf[1] = zero;
+        c->mf[2] = zero;
         p.wl0[0] = p.src;
 }
 
@@ -498,7 +499,7 @@ constexpr unsigned long long kRefreshShare = 2;
 template <int B, class Op, bool kSolo>
 __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, Team tm, BarrierState &bs) {
     const int tid = threadIdx.x;
-    const int wid = tid / kWave;
+    const int wid = wave_id();
     Ctrl *ctrl = p.ctrl;
     Pushers pu{{sm.queue[wid], 0, queue_cap<B>()}, {sm.queue_far[wid], 0, far_cap<B>()}, {}, {}, kInf};
     pu.hq.q = sm.queue_heavy[wid];
@@ -579,7 +580,12 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
                         tm.size == 1 ? ~0ull : wall_clock64() + bs.wd_ticks / kSoloShare,
                         [&](uint32_t i, uint32_t th, uint32_t t) {
                             Op op = make_op<Op>(p, i, th, t, false);
-                            if constexpr (!Op::kFar) op.visited = nullptr;  // the claim alone: one round trip less
+                            if constexpr (Op::kFar) {  // what can_solo leaves: no settled bitmap, no split
+                                op.settled = nullptr;
+                                op.shadow16 = 0;
+                            } else {
+                                op.visited = nullptr;  // the claim alone: one round trip less
+                            }
                             return op;
                         },
                         [&](uint32_t i, uint32_t items) {
@@ -893,7 +899,7 @@ template <int B, class Op>
 __global__ __launch_bounds__(B) void level_kernel(Params p) {
     __shared__ Smem<B> sm;
     const int tid = threadIdx.x;
-    const int wid = tid / kWave;
+    const int wid = wave_id();
     Ctrl *ctrl = p.ctrl;
     const uint32_t it = p.it;
     unsigned long long edges = 0;
@@ -927,7 +933,7 @@ __global__ __launch_bounds__(B) void level_kernel(Params p) {
 template <int B, class Op>
 __global__ __launch_bounds__(B) void hub_level_kernel(Params p) {
     __shared__ Smem<B> sm;
-    const int wid = threadIdx.x / kWave;
+    const int wid = wave_id();
     Ctrl *ctrl = p.ctrl;
     const uint32_t it = p.it;
     uint32_t nh, nchunks;
@@ -946,7 +952,7 @@ __global__ __launch_bounds__(B) void hub_level_kernel(Params p) {
 template <int B>
 __global__ __launch_bounds__(B) void transfer_kernel(Params p, uint32_t far_n, uint32_t t_new) {
     __shared__ Smem<B> sm;
-    const int wid = threadIdx.x / kWave;
+    const int wid = wave_id();
     Ctrl *ctrl = p.ctrl;
     const uint32_t it = p.it;
     const uint32_t tr = p.far_tr;
@@ -985,7 +991,7 @@ __global__ void finish_kernel(Params p, int hit_limit) {
 template <int B>
 __global__ __launch_bounds__(B) void sssp_parent_kernel(Params p) {
     __shared__ Smem<B> sm;
-    const int wid = threadIdx.x / kWave;
+    const int wid = wave_id();
     Pushers pu{{sm.queue[wid], 0, queue_cap<B>()}, {sm.queue_far[wid], 0, far_cap<B>()}, Sink{nullptr, nullptr, 0u, p.ctrl, nullptr},
                Sink{nullptr, nullptr, 0u, p.ctrl, nullptr}, kInf};
     unsigned long long edges = 0;
