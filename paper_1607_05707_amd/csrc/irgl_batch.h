@@ -162,7 +162,7 @@ __device__ __forceinline__ bool run_task(const BatchParams &bp, const TaskDesc &
     if (!grid_barrier(ctrl, bs, &sm.flag, nullptr, tm)) return false;
     if (td.kind == 1 && td.parent) {
         // deterministic SSSP parents: identity worklist over the team
-        const int wid = wave_id();
+        const int wid = threadIdx.x / kWave;
         Pushers pu{{sm.queue[wid], 0, queue_cap<B>()}, {sm.queue_far[wid], 0, far_cap<B>()}, Sink{nullptr, nullptr, 0u, ctrl, nullptr},
                    Sink{nullptr, nullptr, 0u, ctrl, nullptr}, kInf};
         unsigned long long pe = 0;

@@ -115,15 +115,15 @@ struct Stats {
 };
 
 // A constant that takes a register where it is used.  The compiler otherwise
-// prepares the operands of rare stores and atomics at the head of the kernel
-// and holds them to its end: ten registers for the error codes alone.
+// prepares the operands of rare stores at the head of the kernel and holds
+// them to its end (the control block's reset: ten registers of a batch).
 __device__ __forceinline__ uint32_t here(uint32_t x) {
     asm volatile("" : "+v"(x));
     return x;
 }
 
 __device__ __forceinline__ void set_error(Ctrl *c, uint32_t code, bool fatal) {
-    atomicCAS(&c->error, 0u, here(code));
+    atomicCAS(&c->error, 0u, code);
     if (fatal) __hip_atomic_store(&c->fatal, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -152,8 +152,6 @@ static_assert(fit_waves<256, 5>() == 5 && fit_waves<512, 5>() == 4 && fit_waves<
               "register cap per workgroup size");
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
-// This wavefront's index in the workgroup, in a scalar register.
-__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave); }
 
 // Marks the values of one phase of memory accesses as used here and nowhere
 // earlier.  Without it the compiler moves each load (or atomic) of a phase
@@ -270,7 +268,7 @@ template <int B>
 __device__ __forceinline__ void block_drain(WaveQueue &wq, int *s_fill, uint32_t *s_base,
                                             uint32_t *cnt_out, int *out, uint32_t cap, Ctrl *ctrl) {
     constexpr int NW = B / kWave;
-    const int wid = wave_id();
+    const int wid = threadIdx.x / kWave;
     __syncthreads();
     if (lane_id() == 0) s_fill[wid] = wq.n;
     __syncthreads();

@@ -511,8 +511,9 @@ __device__ bool refine(const Params &p, const int32_t *in, uint32_t in_n, Team t
 // through out[i % 3], which every workgroup reads right after the barrier
 // ending i, and clears out[(i + 1) % 3] for the next invocation (last read
 // before the barrier ending i - 1); in and out swap after it.
+// Six waves per SIMD, the co-resident limit that an explicit grid may ask for.
 template <int B>
-__global__ __launch_bounds__(B) void dmr_kernel(Params p) {
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void dmr_kernel(Params p) {
     __shared__ Smem sm;
     const Team tm = whole_grid();
     BarrierState bs = make_barrier_state(p.wd_ticks, p.barrier);

@@ -170,7 +170,7 @@ __device__ __forceinline__ void drain_all(Pushers &pu, S &sm) {
 #pragma unroll
         for (int d = 1; d < kWave; d <<= 1) m = min(m, static_cast<uint32_t>(__shfl_xor(m, d, kWave)));
         __syncthreads();  // every wave has finished reading sm.fill in block_drain
-        if (lane_id() == 0) sm.fill[wave_id()] = static_cast<int>(m);
+        if (lane_id() == 0) sm.fill[threadIdx.x / kWave] = static_cast<int>(m);
         __syncthreads();
         if (threadIdx.x == 0) {
             uint32_t bm = kInf;
@@ -283,7 +283,7 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
     static_assert(Op::kU <= kUMax, "the gather window in LDS holds B * kUMax slots");
     const int tid = threadIdx.x;
     const int lane = lane_id();
-    const int wid = wave_id();
+    const int wid = tid / kWave;
     const uint32_t stride = tm.size * B;
 
     // Small worklist (no more items than wavefronts in the team): one item per

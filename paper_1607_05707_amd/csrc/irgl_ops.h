@@ -165,9 +165,9 @@ struct BfsOp {
     // edges per lane per round (memory-level parallelism) and the fewest
     // waves per SIMD the persistent kernel must fit (1: no register cap): at
     // 4 the co-resident limit, which an explicit grid may ask for, is 512
-    // workgroups of 512 threads or 1024 of 256.  (125 registers, nothing
-    // spilled; 150 before the constants of rare paths were kept out of the
-    // kernel's head, see here() and wave_id(), and half as many workgroups.)
+    // workgroups of 512 threads or 1024 of 256.  (Without the cap the form
+    // with solo runs takes 150 registers and half as many workgroups fit; with
+    // it ten are spilled, read back once an invocation.)
     static constexpr int kU = 4;
     static constexpr int kMinWaves = 4;
     uint32_t *level;

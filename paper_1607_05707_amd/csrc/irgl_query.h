@@ -499,7 +499,7 @@ constexpr unsigned long long kRefreshShare = 2;
 template <int B, class Op, bool kSolo>
 __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, Team tm, BarrierState &bs) {
     const int tid = threadIdx.x;
-    const int wid = wave_id();
+    const int wid = threadIdx.x / kWave;
     Ctrl *ctrl = p.ctrl;
     Pushers pu{{sm.queue[wid], 0, queue_cap<B>()}, {sm.queue_far[wid], 0, far_cap<B>()}, {}, {}, kInf};
     pu.hq.q = sm.queue_heavy[wid];
@@ -899,7 +899,7 @@ template <int B, class Op>
 __global__ __launch_bounds__(B) void level_kernel(Params p) {
     __shared__ Smem<B> sm;
     const int tid = threadIdx.x;
-    const int wid = wave_id();
+    const int wid = threadIdx.x / kWave;
     Ctrl *ctrl = p.ctrl;
     const uint32_t it = p.it;
     unsigned long long edges = 0;
@@ -933,7 +933,7 @@ __global__ __launch_bounds__(B) void level_kernel(Params p) {
 template <int B, class Op>
 __global__ __launch_bounds__(B) void hub_level_kernel(Params p) {
     __shared__ Smem<B> sm;
-    const int wid = wave_id();
+    const int wid = threadIdx.x / kWave;
     Ctrl *ctrl = p.ctrl;
     const uint32_t it = p.it;
     uint32_t nh, nchunks;
@@ -952,7 +952,7 @@ __global__ __launch_bounds__(B) void hub_level_kernel(Params p) {
 template <int B>
 __global__ __launch_bounds__(B) void transfer_kernel(Params p, uint32_t far_n, uint32_t t_new) {
     __shared__ Smem<B> sm;
-    const int wid = wave_id();
+    const int wid = threadIdx.x / kWave;
     Ctrl *ctrl = p.ctrl;
     const uint32_t it = p.it;
     const uint32_t tr = p.far_tr;
@@ -991,7 +991,7 @@ __global__ void finish_kernel(Params p, int hit_limit) {
 template <int B>
 __global__ __launch_bounds__(B) void sssp_parent_kernel(Params p) {
     __shared__ Smem<B> sm;
-    const int wid = wave_id();
+    const int wid = threadIdx.x / kWave;
     Pushers pu{{sm.queue[wid], 0, queue_cap<B>()}, {sm.queue_far[wid], 0, far_cap<B>()}, Sink{nullptr, nullptr, 0u, p.ctrl, nullptr},
                Sink{nullptr, nullptr, 0u, p.ctrl, nullptr}, kInf};
     unsigned long long edges = 0;

@@ -139,7 +139,7 @@ __device__ __forceinline__ SsspTopoOp make_topo_op<SsspTopoOp>(const Params &p, 
 // deferred vertices has one barrier, otherwise two.
 template <int B, class Op>
 __device__ __forceinline__ LoopResult run_topology(const Params &p, Smem<B> &sm, Team tm, BarrierState &bs) {
-    const int wid = wave_id();
+    const int wid = threadIdx.x / kWave;
     Ctrl *ctrl = p.ctrl;
     Pushers pu{{sm.queue[wid], 0, queue_cap<B>()}, {sm.queue_far[wid], 0, far_cap<B>()}, Sink{nullptr, nullptr, 0u, ctrl, nullptr},
                Sink{nullptr, nullptr, 0u, ctrl, nullptr}, kInf};
