@@ -390,7 +390,9 @@ typedef struct irgl_batch_config {
     int32_t t_grid;
     uint32_t delta;    /* SSSP near/far step for every task (0 = per-graph default) */
     uint32_t watchdog_ms;
-    int32_t grid;      /* workgroups (0 = co-resident limit); rounded down to whole teams */
+    int32_t grid;      /* workgroups, at most the co-resident limit (0 = one per compute
+                          unit, two for a batch of many tasks per team); rounded down
+                          to whole teams */
     uint32_t barrier;  /* team-barrier scheme, as irgl_config.barrier */
     uint32_t gang_edges; /* open batches: a task on a graph with at least this many
                             edges runs on the whole grid (all teams together, in

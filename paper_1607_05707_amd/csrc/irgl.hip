@@ -830,6 +830,22 @@ irgl_status batch_grid(int dev, int requested, int *grid, bool server) {
     return coresident_grid(batch_kernel<B>, B, dev, requested, grid);
 }
 
+// Workgroups of a batch or server whose grid is left at 0: one per compute
+// unit, or two for a batch of at least kTasksPerTeam tasks per team of that
+// grid.  More teams share the memory, so each task takes longer; they pay only
+// where the tasks, and not the longest one, decide when the batch ends.  ms at
+// one / two workgroups per unit, teams of 16 (256 threads, then 512): 80 tasks
+// 12.0 / 12.7, 8.9 / 9.5; 128 tasks 12.2 / 12.9, 9.1 / 9.9; 192 tasks 15.2 /
+// 15.3, 12.9 / 12.9; 320 tasks 31.4 / 24.9, 26.6 / 24.5 (and of those with
+// R-MAT 20 in place of 18, 32.6 at four of 256 against 29.1 at two).  A
+// server, whose tasks come one by one: 408 queries per second at one, 406 at
+// two, 366 at three.
+constexpr int kTasksPerTeam = 12;
+int default_team_grid(int limit, int cus, int team, int32_t ntasks) {
+    const int teams = std::max(1, cus / team);
+    return std::min(limit, ntasks / kTasksPerTeam >= teams ? 2 * cus : cus);
+}
+
 // One team's (or the gang's) scratch region for graphs of at most nmax
 // vertices / mmax edges: control block, claimed descriptor (and gang
 // record), worklists, SSSP arrays, bitmap and grid-tier list.
@@ -868,6 +884,12 @@ irgl_status team_layout(int64_t nmax, int64_t mmax, bool any_sssp, bool any_bfs,
         default: st = batch_grid<1024>(dev, c.grid, &grid, server); break;
     }
     if (st) return st;
+    if (!c.grid) {
+        DeviceInfo di;
+        st = device_info(dev, &di);
+        if (st) return st;
+        grid = default_team_grid(grid, di.cus, c.team, server ? 0 : records);
+    }
     const int team = std::min(c.team, grid);
     L.team = team;
     L.teams = grid / team;

@@ -51,6 +51,19 @@ struct BatchParams {
     uint32_t barrier;  // grid-barrier coherence scheme (kBar*)
 };
 
+// A descriptor in scalar registers.  Its words come from memory, so the
+// compiler holds a copy of each per lane unless told that they are the same
+// for the whole wavefront (batch_kernel<512>: 253 vector registers).
+__device__ __forceinline__ TaskDesc uniform_desc(const TaskDesc &t) {
+    struct Words {
+        int w[sizeof(TaskDesc) / 4];
+    };
+    Words x = __builtin_bit_cast(Words, t);
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(TaskDesc) / 4; ++k) x.w[k] = __builtin_amdgcn_readfirstlane(x.w[k]);
+    return __builtin_bit_cast(TaskDesc, x);
+}
+
 __device__ __forceinline__ Params task_params(const BatchParams &bp, const TaskDesc &t, char *base) {
     Params p;
     const int m = __builtin_amdgcn_readfirstlane(t.row_ptr[t.n]);
@@ -176,8 +189,11 @@ __device__ __forceinline__ bool run_task(const BatchParams &bp, const TaskDesc &
     return load_agent(&ctrl->fatal) == 0u;  // uniform: set before the last barrier
 }
 
+// Four waves per SIMD, the co-resident limit that grids and teams are sized
+// from: 1024 workgroups of 256 threads, 512 of 512.
 template <int B>
-__global__ __launch_bounds__(B) void batch_kernel(BatchParams bp) {
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(fit_waves<B, 4>()))) void batch_kernel(
+    BatchParams bp) {
     __shared__ Smem<B> sm;
     __shared__ int s_task;
     const uint32_t team_id = blockIdx.x / static_cast<uint32_t>(bp.team);
@@ -199,7 +215,7 @@ __global__ __launch_bounds__(B) void batch_kernel(BatchParams bp) {
         const int t = s_task;
         if (t >= bp.ntasks) return;  // uniform across the team: queue drained
         LoopResult r;
-        if (!run_task<B>(bp, bp.tasks[t], base, tm, bs, sm, r)) return;
+        if (!run_task<B>(bp, uniform_desc(bp.tasks[t]), base, tm, bs, sm, r)) return;
     }
 }
 
@@ -305,8 +321,12 @@ __device__ __forceinline__ void report_task(const ServerParams &sp, const TaskDe
     __hip_atomic_store(&sp.done[slot], ticket + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Three waves per SIMD: 768 workgroups of 256 threads.  (One run_task serves
+// the team's tasks and the gangs: two copies of both loops took 254 registers
+// and 22 more.)
 template <int B>
-__global__ __launch_bounds__(B) void server_kernel(ServerParams sp) {
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(fit_waves<B, 3>()))) void server_kernel(
+    ServerParams sp) {
     __shared__ Smem<B> sm;
     __shared__ uint32_t s_ticket;
     const BatchParams &bp = sp.bp;
@@ -414,7 +434,8 @@ __global__ __launch_bounds__(B) void server_kernel(ServerParams sp) {
         __syncthreads();
         const uint32_t ticket = s_ticket;
         if (ticket == kQuit) return;  // uniform across the team
-        if (ticket == kGang) {
+        const bool gang_task = ticket == kGang;
+        if (gang_task) {
             // every team is here: the gang region's descriptor and kind are visible
             if (!grid_barrier(gctrl, gbs, &sm.flag, nullptr, grid)) {
                 if (leader && gang_claim != kNone) report_task(sp, gi->desc, gang_claim, false);
@@ -434,21 +455,20 @@ __global__ __launch_bounds__(B) void server_kernel(ServerParams sp) {
                 if (end) return;
                 continue;
             }
-            const TaskDesc td = gi->desc;
-            const uint32_t gticket = gi->ticket;
-            LoopResult r;
-            const bool ok = run_task<B>(sp.gang, td, gbase, grid, gbs, sm, r);
-            if (grid.id == 0 && threadIdx.x == 0) {
-                report_task(sp, td, gticket, ok);
-                atomicAnd(sp.head, ~kPending);
-            }
-            if (!ok) return;
-            continue;
         }
-        const TaskDesc td = *mine;
+        // the team's task on its region, or the gang's on the gang region
+        const TaskDesc td = uniform_desc(gang_task ? gi->desc : *mine);
+        const uint32_t reported = gang_task ? gi->ticket : ticket;
+        const Team who = gang_task ? grid : tm;
+        BarrierState wait = gang_task ? gbs : bs;
         LoopResult r;
-        const bool ok = run_task<B>(bp, td, base, tm, bs, sm, r);
-        if (leader) report_task(sp, td, ticket, ok);
+        const bool ok = run_task<B>(gang_task ? sp.gang : bp, td, gang_task ? gbase : base, who, wait, sm, r);
+        if (gang_task) gbs = wait;
+        else bs = wait;
+        if (who.id == 0 && threadIdx.x == 0) {
+            report_task(sp, td, reported, ok);
+            if (gang_task) atomicAnd(sp.head, ~kPending);
+        }
         if (!ok) return;
     }
 }
