@@ -965,22 +965,31 @@ irgl_status launch_batch(const BatchParams &bp, int grid, hipStream_t s) {
 
 uint32_t task_delta(const irgl_graph_s *g, uint32_t override_delta);
 
+// The direction choice of a batched BFS on the graph (0: top-down only).
+uint32_t task_alpha(const irgl_graph_s *g) {
+    const uint32_t alpha = (g->flags & IRGL_SYMMETRIC) ? do_alpha_rule(g) : IRGL_DO_OFF;
+    return alpha == IRGL_DO_OFF ? 0u : alpha;
+}
+
 // About the nanoseconds a task takes a team of 16 workgroups of 512 threads,
-// for the order in which teams take them (measured, ms: SSSP 2.79 at n =
-// 530,000, m = 4.1M, 1.80 at 88,000 and 2.7M, 0.61 at 10,000 and 0.29M; BFS
-// on symmetric graphs 1.51 at 745,000 and 4.5M, 0.92 at 904,000 and 20M, 0.34
-// at 262,000 and 7.6M, 1.4 there when it may not go bottom-up).
+// for the order in which teams take them.  A BFS that may go bottom-up scans
+// few of the entries, any other scans all.  Measured, one team alone, us (n,
+// m): SSSP 874 (30,000, 0.72M), 1407 (262,000, 1.0M, road-like), 2930
+// (500,000, 5.5M, directed), 3459 (1M, 4.2M), 7225 (904,000, 20M), 16382 (1M,
+// 31M, skewed); BFS that may go bottom-up 254 (100,000, 0.6M), 291 (262,000,
+// 7.6M, skewed), 771 (1M, 31M, skewed), 1093 (904,000, 20M), 1243 (745,000,
+// 4.5M); top-down 501 (200,000, 1.2M, directed), 577 (260,000, 1.1M), 1224
+// (500,000, 5.5M, directed), 1365 (1M, 4.0M, road-like), 1599 (1M, 4.2M).
 int64_t task_cost(const irgl_task &t) {
     const int64_t n = t.g->n, m = t.g->m;
     if (t.kind == IRGL_KIND_SSSP) return 450000 + m / 2 + n;
-    return 200000 + n + ((t.g->flags & IRGL_SYMMETRIC) ? 0 : m / 6);
+    return 200000 + n + (task_alpha(t.g) ? 0 : m / 6);
 }
 
 void fill_desc(TaskDesc &d, const irgl_task &t, Stats *stats, uint32_t delta_override, bool gang = false) {
     std::memset(&d, 0, sizeof(d));
     d.gang = gang ? 1u : 0u;
-    d.do_alpha = t.kind == IRGL_KIND_BFS && (t.g->flags & IRGL_SYMMETRIC) ? do_alpha_rule(t.g) : 0u;
-    if (d.do_alpha == IRGL_DO_OFF) d.do_alpha = 0u;
+    d.do_alpha = t.kind == IRGL_KIND_BFS ? task_alpha(t.g) : 0u;
     d.row_ptr = t.g->orig_row_ptr;
     d.col = t.g->orig_col;
     d.w = t.g->orig_w;
