@@ -341,8 +341,13 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
     const uint32_t tsz = (Op::kFar && cnt_in < stride)
                              ? min(static_cast<uint32_t>(B), max(128u, (cnt_in + tm.size - 1) / tm.size))
                              : static_cast<uint32_t>(B);
-    // The next tile is reserved while this one's rows are looked up, and its
-    // items are read before this one's edges are relaxed.
+    // A worklist's next tile is reserved while this one's rows are looked up,
+    // and its items are read before this one's edges are relaxed.  A sweep
+    // over all vertices, most of whose tiles hold no edge to relax, takes it
+    // when it is done with this one (topology-driven us, reserved first / last:
+    // road-like 512^2 BFS at 256 threads 1874 / 1509, SSSP at 512 1561 / 1398;
+    // uniform 600,000 x 12 592 / 539, 2532 / 2182).
+    constexpr bool kAhead = Op::kPush;
     uint32_t tile = tm.id;
     const auto item = [&](uint32_t t) -> int {
         const uint32_t i = t * tsz + static_cast<uint32_t>(tid);
@@ -353,7 +358,7 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
     for (;;) {
         if (tile * tsz >= cnt_in) break;  // uniform across the workgroup
         uint32_t next_tile = tile + tm.size;
-        if (tile_ctr && tid == 0) next_tile = tm.size + atomicAdd(tile_ctr, 1u);
+        if (kAhead && tile_ctr && tid == 0) next_tile = tm.size + atomicAdd(tile_ctr, 1u);
         int r0 = 0, r1 = 0;
         uint32_t val = 0;
         bool hp = false, ex = false;
@@ -433,7 +438,7 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
         // workgroup needs ceil(total / (B*U)) rounds whatever the degree mix.
         const int incl = wave_inclusive_scan(deg);
         if (lane == kWave - 1) sm.wsum[wid] = incl;
-        if (tid == 0) sm.tile = next_tile;
+        if (kAhead && tid == 0) sm.tile = next_tile;
         __syncthreads();
         int total = 0, wpre = 0;
 #pragma unroll
@@ -446,8 +451,10 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
         sm.gr0[tid] = r0;
         sm.vtx[tid] = v;
         sm.vval[tid] = val;
-        tile = sm.tile;
-        v = item(tile);
+        if (kAhead) {
+            tile = sm.tile;
+            v = item(tile);
+        }
         __syncthreads();
         for (int done = 0; done < total; done += kChunk) {
             int e[Op::kU], sv[Op::kU];
@@ -467,7 +474,12 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
             }
             relax_and_push<Op::kU>(op, col, e, act, sv, sval, pu);
         }
+        if (!kAhead && tid == 0) sm.tile = tile_ctr ? tm.size + atomicAdd(tile_ctr, 1u) : next_tile;
         __syncthreads();  // the scan arrays are rewritten by the next tile
+        if (!kAhead) {
+            tile = sm.tile;
+            v = item(tile);
+        }
     }
 }
 
