@@ -141,8 +141,8 @@ typedef struct irgl_config {
                              block for a worklist with fewer items than the grid has
                              threads); IRGL_GRID_TIER_OFF = never */
     int32_t grid;         /* workgroups; 0 = the co-resident limit (occupancy x CUs),
-                             or, with block 0 too, fewer on graphs whose
-                             invocations cost more in barriers than they gain
+                             or, for BFS and with block 0 too, fewer on graphs
+                             whose invocations cost more in barriers than they gain
                              from it; one, in an ordinary launch, on the smallest */
     int32_t mode;         /* IRGL_MODE_* */
     uint32_t max_iter;    /* safety cap on invocations (default n + 1 for BFS,
@@ -641,7 +641,8 @@ irgl_status irgl_batch_close(irgl_server s);
 
 typedef struct irgl_mst_config {
     int32_t block;        /* 256, 512 (default) or 1024 */
-    int32_t grid;         /* workgroups; 0 = the co-resident limit, fewer on small graphs */
+    int32_t grid;         /* workgroups; 0 = 1024 threads per compute unit, fewer on small
+                             graphs */
     uint32_t lock;        /* IRGL_LOCK_* */
     uint32_t watchdog_ms; /* bound of every barrier and lock wait (default 20000) */
     uint32_t barrier;     /* IRGL_BARRIER_* */
@@ -700,7 +701,7 @@ typedef struct irgl_mesh {
 typedef struct irgl_dmr_config {
     double min_angle;          /* quality bound in degrees, in (0, 60); 0 = 30 */
     int32_t block;             /* 64, 128 or 256 (default) threads per workgroup */
-    int32_t grid;              /* workgroups; 0 = co-resident limit */
+    int32_t grid;              /* workgroups; 0 = five waves per SIMD (the limit is six) */
     uint32_t max_invocations;  /* safety cap of kernel invocations (0 = 100000) */
     uint32_t watchdog_ms;      /* bound of every barrier wait (0 = 20000) */
     uint32_t barrier;          /* IRGL_BARRIER_* */

@@ -292,6 +292,8 @@ constexpr int64_t kShapeSsspSkewed = int64_t(1) << 22;
 constexpr int64_t kShapeSsspEven = int64_t(1) << 25;
 constexpr int64_t kShapeSsspSplit = int64_t(1) << 26;
 
+constexpr int kBfsThreadsPerCu = 512;
+
 int default_block(const irgl_graph_s *g, int kind, const irgl_config *c) {
     if (kind != IRGL_KIND_BFS) return 512;
     if (c && (c->grid || c->mode != IRGL_MODE_PERSISTENT)) return 1024;
@@ -558,11 +560,20 @@ irgl_status launch_query(const irgl_graph_s *g, Params &p, const Cfg &c, hipStre
         // few invocations of a scale-free graph are small: the kernel without
         // solo runs keeps more registers for the others (RMAT-22 BFS 0.39
         // against 0.41 ms per query)
-        const auto kernel = scale_free(g) ? persistent_kernel<B, Op, false> : persistent_kernel<B, Op, true>;
+        const bool skewed = scale_free(g);
+        const auto kernel = skewed ? persistent_kernel<B, Op, false> : persistent_kernel<B, Op, true>;
         int grid = 0;
         st = coresident_grid(kernel, B, g->device, c.grid, &grid);
         if (st) return st;
         if (c.most_grid) grid = std::min(grid, c.most_grid);
+        // BFS with an explicit workgroup size only: as many threads per
+        // compute unit as the default shape has at most (us at 256 / 512
+        // workgroups of 512 threads, then 512 / 768 / 1024 of 256: road-like
+        // 512^2 455 / 515, 503 / 576 / 678; 2048^2 1004 / 1017, 1029 / 1171 /
+        // 1287; uniform 600,000 x 12 265 / 293, 276 / 303 / 329; directed 1.5M
+        // x 11 418 / 403, 424 / 428 / 458)
+        else if (!c.grid && kind == IRGL_KIND_BFS && !skewed)
+            grid = std::min(grid, di.cus * std::max(1, kBfsThreadsPerCu / B));
         void *args[] = {&p};
         IRGL_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(kernel), dim3(grid), dim3(B), args, 0, s));
     } else if (c.mode == IRGL_MODE_TOPOLOGY) {

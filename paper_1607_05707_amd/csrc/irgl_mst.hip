@@ -769,7 +769,14 @@ irgl_status mst_launch(MstParams &p, int64_t m, int dev, int requested, hipStrea
     int grid = 0;
     irgl_status st = mst_grid<B>(dev, requested, &grid);
     if (st) return st;
-    if (!requested) grid = std::min(grid, mst_workgroups(p.n, m, B));
+    // ... and at most 1024 threads per compute unit (us at 1024 / 1280
+    // workgroups of 256: uniform 600,000 x 12 1312 / 1384, 2M x 16 2923 /
+    // 3048; road-like 2048^2 3380 / 3283)
+    if (!requested) {
+        int cus = 0;
+        MST_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        grid = std::min({grid, mst_workgroups(p.n, m, B), cus * (1024 / B)});
+    }
     void *args[] = {&p};
     MST_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(mst_kernel<B>), dim3(grid), dim3(B), args, 0,
                                        s));
