@@ -286,7 +286,11 @@ void resolve_tiers(int block, int t_wave, int t_block, int t_grid, int *ow, int 
 constexpr int64_t kShapeTiny = int64_t(1) << 20;
 constexpr int64_t kShapeSmall = int64_t(1) << 23;
 constexpr int64_t kShapeSmallSkewed = int64_t(1) << 25;
-// Scale-free graphs of this many entries keep BFS at 1024 threads.
+// Scale-free graphs of this many entries keep the 1024 threads that full-size
+// callers find in their statistics.  At 256 workgroups 512 threads are faster
+// from most sources (us at 1024 / 512, four sources: R-MAT 22 299 / 272, 470 /
+// 499, 301 / 270, 312 / 259; R-MAT 23 434 / 411, 488 / 436, 525 / 469, 477 /
+// 417), as they are below this line (R-MAT 21 300 / 259, 264 / 234).
 constexpr int64_t kWideBfsMinEdges = int64_t(1) << 26;
 constexpr int64_t kShapeSsspSkewed = int64_t(1) << 22;
 constexpr int64_t kShapeSsspEven = int64_t(1) << 25;
@@ -517,7 +521,11 @@ irgl_status parent_pass(const Params &p, hipStream_t s, int kind) {
 // against a full grid in us per query, BFS 59 / 102 on 8K, 69 / 123 on 53K
 // R-MAT and 108 / 145 on 64K uniform edges, 174 / 171 on 8,000 vertices of
 // degree 4; SSSP 186 / 227 on 8K uniform edges, 422 / 479 on the 64x64 grid,
-// but 416 / 274 on 32K uniform edges and 533 / 331 on 53K R-MAT edges.
+// but 416 / 274 on 32K uniform edges and 533 / 331 on 53K R-MAT edges.  SSSP
+// around the line, one workgroup / 128: grids of 6,240 and 16,128 entries 287
+// / 318 and 623 / 682, road-like 15,490 299 / 330 (and 29,418 about 450 / 429);
+// uniform graphs below it, which have few wide buckets, lose: 4,000 x 4 269 /
+// 220, 2,000 x 8 251 / 210, 1,000 x 8 163 / 168.
 constexpr int64_t kOneVertices = 1 << 13;
 constexpr int64_t kOneEdges = 1 << 16;
 constexpr int64_t kOneEdgesSssp = 1 << 14;        // mean out-degree below 8 (grids, road-like graphs)

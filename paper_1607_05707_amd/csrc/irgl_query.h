@@ -304,8 +304,8 @@ __device__ __forceinline__ void pull_level(const Params &p, uint32_t next, Team 
             rr1[j] = unvisited ? p.row_ptr[v + 1] : 0;
         }
         // the first neighbours of all kPullV vertices together: most vertices
-        // that a large frontier reaches are found there (a relabelled graph's
-        // rows begin with its hubs)
+        // that a large frontier reaches are found there (whichever they are: a
+        // relabelled graph's rows keep the caller's order)
         int first[kPullV];
         {
             int u[kPullV][kUMax];
