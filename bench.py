@@ -606,11 +606,15 @@ def main() -> int:
     # bytes count a top-down traversal; bottom-up invocations scan fewer
     # entries, so its measured traffic can sit below them.
     from paper_1607_05707_amd import profiling
-    kernel_of = {k: f"persistent_kernel<{blocks[k]}, irgl::{['BfsOp', 'SsspOp'][k]}>" for k in kinds}
+    op_of = ["BfsOp", "SsspOp"]
+    kernel_of = {k: f"persistent_kernel<{blocks[k]}, irgl::{op_of[k]}>" for k in kinds}
     traffic_of = {}
     for k in kinds:
         rec = profiling.load_traffic(os.path.join(ROOT, "profiles", f"traffic_{args.workload}_{names_k[k]}.json"))
-        traffic_of[k] = int(rec["traffic_bytes_per_launch"]) if rec and rec.get("kernel") == kernel_of[k] else None
+        traffic_of[k] = None
+        if rec and profiling.is_query_kernel(rec["kernel"], blocks[k], op_of[k]):
+            traffic_of[k] = int(rec["traffic_bytes_per_launch"])
+            kernel_of[k] = rec["kernel"]
         kind_summary[k]["roofline_frac"] = round(kind_summary[k]["alg_gbs"] / PEAK_HBM_GBS, 4)
         kind_summary[k]["traffic_bytes_per_launch"] = traffic_of[k]
         kind_summary[k]["traffic_over_alg"] = (round(traffic_of[k] / kind_summary[k]["alg_bytes_per_query"], 3)

@@ -8,7 +8,7 @@ per-dispatch averages of the kernel are its measured HBM traffic per launch.
 
   python -m paper_1607_05707_amd.profiling traffic \\
       --fetch-db F_results.db --write-db W_results.db --calib-mb 1024 \\
-      --kernel 'persistent_kernel<256, irgl::SsspOp>' --workload rmat22 \\
+      --kernel 'persistent_kernel<512, irgl::SsspOp, false>' --workload rmat22 \\
       --command '...' --out profiles/traffic_rmat22_sssp.json
 
 The JSON records a digest of the HIP sources; bench.py reports the traffic
@@ -111,6 +111,14 @@ def load_traffic(path: str):
     if rec.get("source_digest") != source_digest():
         return None
     return rec
+
+
+def is_query_kernel(name: str, block: int, op: str) -> bool:
+    """Whether a recorded kernel is the outlined single-query kernel of `op`
+    (BfsOp, SsspOp) with `block` threads, in either form (with solo runs or
+    without: the graph decides)."""
+    head = f"persistent_kernel<{block}, irgl::{op}"
+    return name in (head + ", true>", head + ", false>")
 
 
 def main(argv=None) -> int:
