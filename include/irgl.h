@@ -533,7 +533,7 @@ typedef struct irgl_pipe_io {
     int32_t block;           /* 0 = the largest size of T_control; else a member of it */
     uint32_t max_invocations; /* safety cap (0 = 8 n + 64): IRGL_ERR_ITERATION_LIMIT */
     uint32_t watchdog_ms;    /* 0 = 20000 */
-    int32_t grid;            /* workgroups (0 = co-resident limit) */
+    int32_t grid;            /* workgroups (0 = 512 threads per compute unit) */
     uint32_t force_retry;    /* test knob: 1 = in the first round of every MST_FINDMIN invocation
                                 the vertices with odd ids take the Else branch (retry) as if
                                 their lock were busy; results are unchanged */

@@ -679,7 +679,14 @@ irgl_status launch(Params &p, int dev, int requested, hipStream_t s) {
     per_cu = std::min(per_cu, std::max(1, 24 / (B / kWave)));
     const int limit = per_cu * cus;
     if (limit <= 0 || requested < 0 || requested > limit) return IRGL_ERR_CONFIG;
-    const int grid = requested ? requested : limit;
+    // By default 512 threads per compute unit: the limit follows the registers
+    // that the compiler happens to take, and more workgroups only cost every
+    // barrier (BFS, us at 512 threads per unit / at the limit: road-like 512^2
+    // at 64 threads 1362 / 2736, 128 882 / 1520, 256 672 / 884, 512 633 / 701;
+    // uniform 300,000 x 8 487 / 975, 318 / 555, 249 / 327, 235 / 257; R-MAT 19
+    // 1242 / 1630, 1086 / 1270, 1142 / 1218, 1270 / 1290; forest at 256, road-like
+    // 5273 / 5745, uniform 5802 / 6484)
+    const int grid = requested ? requested : std::min(limit, cus * std::max(1, 512 / B));
     void *args[] = {&p};
     PIPE_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(pipe_kernel<B>), dim3(grid), dim3(B), args, 0, s));
     return IRGL_OK;

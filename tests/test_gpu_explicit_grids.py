@@ -72,3 +72,25 @@ def test_refinement_grids(irgl, cus, block, k):
     assert st["final_bad"] == 0
     om.check_mesh(dm.pts[:dm.npts].cpu().numpy(), dm.tri[:dm.ntri].cpu().numpy(), dm.nbr[:dm.ntri].cpu().numpy(),
                   input_pts=m.input_pts, min_angle=30.0)
+
+
+def test_grids_left_at_zero(irgl, cus):
+    """The workgroups of launches whose grid is left at 0 do not follow the limits."""
+    g = gg.uniform_random(60000, 6.0, seed=3, weight_seed=4)
+    rp, col, _ = g.numpy()
+    src = gg.pick_sources(g, 1, seed=2)[0]
+    ref = oracle.bfs(rp, col, src)[0]
+    hg = irgl.upload(g.to("cuda"))
+    for block in (256, 512, 1024):
+        _, _, st = irgl.query(hg, BFS, src, cfg={"block": block})
+        assert st["grid"] == cus * max(1, 512 // block)
+    weight, _, _, st = irgl.mst(hg, cfg={"block": 256})
+    assert weight == oracle.kruskal(*g.numpy())[0] and st["grid"] <= cus * 4
+    level = torch.empty(g.n, dtype=torch.int32, device="cuda")
+    for block in (64, 128, 256, 512, 1024):
+        print(f"[case] pipe {block}", flush=True)
+        stats = irgl.stats_tensor(torch.device("cuda:0"))
+        irgl.irgl_pipe_run(hg, irgl.pipe_bfs_program(), src=src, level=level, block=block, stats=stats)
+        st = irgl.read_stats(stats)
+        assert st["status"] == 0 and st["grid"] == cus * max(1, 512 // block)
+        np.testing.assert_array_equal(irgl.as_u32_numpy(level), ref)
