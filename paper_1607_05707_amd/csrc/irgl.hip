@@ -530,9 +530,22 @@ constexpr int64_t kOneVertices = 1 << 13;
 constexpr int64_t kOneEdges = 1 << 16;
 constexpr int64_t kOneEdgesSssp = 1 << 14;        // mean out-degree below 8 (grids, road-like graphs)
 constexpr int64_t kOneEdgesSsspDense = 1 << 13;  // others
+// A BFS that stays top-down scans every entry, and worklists of thousands of
+// vertices with it: us on one workgroup / 64, directed graphs of 16,000
+// entries 74 / 92, 96 / 111, 135 / 149, of 24,000 102 / 102, of 32,000 122 /
+// 109, 166 / 124, of 64,000 206 / 115; uniform of degree 3, 24,000, 153 / 131.
+// Grids and roads, whose worklists stay small, keep the larger line (30,624
+// entries 425 / 460, 29,418 150 / 177).  A row that one workgroup takes alone
+// (star of 8,000: SSSP 95 / 61) goes to many.
+constexpr int64_t kOneEdgesTopDown = 1 << 14;
+constexpr uint32_t kOneNarrowDegree = 8;
+constexpr uint32_t kOneRow = 4096;
 bool one_workgroup(const irgl_graph_s *g, const Cfg &c, int kind) {
     // an explicit grid is kept, and so is a watchdog that ends every wait
-    const int64_t most = kind != IRGL_KIND_SSSP ? kOneEdges
+    const bool bottom_up = kind == IRGL_KIND_BFS && c.do_alpha != 0;
+    if (!bottom_up && g->max_degree > kOneRow) return false;
+    const bool narrow = g->max_degree != 0 && g->max_degree <= kOneNarrowDegree;
+    const int64_t most = kind != IRGL_KIND_SSSP ? (bottom_up || narrow ? kOneEdges : kOneEdgesTopDown)
                          : g->m < 8 * static_cast<int64_t>(g->n) ? kOneEdgesSssp
                                                                  : kOneEdgesSsspDense;
     return g->n <= kOneVertices && g->m <= most && c.grid == 0 && c.watchdog_ms != IRGL_WATCHDOG_IMMEDIATE;
