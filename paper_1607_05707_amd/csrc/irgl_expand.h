@@ -332,13 +332,15 @@ __device__ __forceinline__ void expand(const int32_t *__restrict__ in, uint32_t 
     if (t_grid > B && cnt_in < stride) t_grid = B;
     // Tiles of B items: first one per workgroup, then (with tile_ctr) taken
     // from a shared counter, so that workgroups with light tiles take more.
-    // SSSP: such a worklist would fill only cnt_in / B workgroups, and one
-    // tile of B medium-degree vertices (a light phase just after the first
-    // hubs) then keeps one workgroup busy for a tenth of the query; its tiles
-    // hold ceil(cnt_in / team size) items instead (at least 128), so that
-    // every workgroup takes a share.  Consecutive items stay on consecutive
-    // threads (pushes of one wavefront are often neighbouring vertices).
-    const uint32_t tsz = (Op::kFar && cnt_in < stride)
+    // Such a worklist would fill only cnt_in / B workgroups, and one tile of B
+    // medium-degree vertices (an SSSP light phase just after the first hubs)
+    // then keeps one workgroup busy for a tenth of the query; its tiles hold
+    // ceil(cnt_in / team size) items instead (at least 128), so that every
+    // workgroup takes a share.  Consecutive items stay on consecutive threads
+    // (pushes of one wavefront are often neighbouring vertices).  (BFS took
+    // whole tiles: 100,000 x 30 on 128 workgroups, whose second worklist has
+    // just more items than there are wavefronts, 188 against 137 us.)
+    const uint32_t tsz = (Op::kPush && cnt_in < stride)
                              ? min(static_cast<uint32_t>(B), max(128u, (cnt_in + tm.size - 1) / tm.size))
                              : static_cast<uint32_t>(B);
     // A worklist's next tile is reserved while this one's rows are looked up,
