@@ -533,7 +533,9 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
     // settled bitmap.  A team invocation follows each, so that a worklist the
     // first workgroup leaves (too many items or edges) makes progress.
     const bool can_solo = kSolo && p.solo_items > 0 && !split && !(Op::kFar && p.visited);
-    bool solo_next = can_solo;
+    // Team invocations before the next solo run: one after a run, more after a
+    // run of a few invocations, which cost the team a barrier more than it saved.
+    uint32_t solo_wait = can_solo ? 0u : ~0u;
     uint32_t rot = 0;  // rotates the counters: team invocations and solo runs so far
 
     for (;;) {
@@ -553,7 +555,7 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
         // uniform: settled counters.  The out-degree sum of the worklist, where
         // it is known, says beforehand that one workgroup is not enough.
         const bool solo =
-            kSolo && solo_next && cnt_in > 0 && cnt_in <= p.solo_items &&
+            kSolo && solo_wait == 0 && cnt_in > 0 && cnt_in <= p.solo_items &&
             (!can_pull || __hip_atomic_load(&ctrl->mf[rot % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= kSoloEdges);
         if (lead) {
             store_agent(&ctrl->cnt[(rot + 2) % 3], 0u);
@@ -618,14 +620,15 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
                     }
                 }
                 if (!grid_barrier(ctrl, bs, &sm.flag, p.abort_flag, tm)) break;
+                const uint32_t it_before = it;
                 it = load_agent(&slot->it);
+                solo_wait = it - it_before >= kSoloWorth ? 1u : kSoloHold;
                 tr = load_agent(&slot->tr);
                 thresh = load_agent(&slot->thresh);
                 r.items = __hip_atomic_load(&slot->items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 m_seen = __hip_atomic_load(&slot->m_seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 bitmaps_current = false;
                 pull = false;
-                solo_next = false;
                 ++rot;
                 const int32_t *t = in;
                 in = out;
@@ -633,7 +636,7 @@ __device__ __forceinline__ LoopResult run_iterate(const Params &p, Smem<B> &sm, 
                 continue;
             }
         }
-        solo_next = can_solo;
+        if (kSolo && solo_wait > 0) --solo_wait;
         r.items += cnt_in;
         r.max_frontier = max(r.max_frontier, cnt_in);
         if (lead) {

@@ -31,6 +31,9 @@ constexpr uint32_t kSoloEdges = 4096;
 constexpr uint32_t kSoloSteps = 512;
 constexpr uint32_t kSoloClock = 8;
 constexpr unsigned long long kSoloShare = 4;
+// After a run of fewer than kSoloWorth invocations kSoloHold team invocations follow.
+constexpr uint32_t kSoloWorth = 3;
+constexpr uint32_t kSoloHold = 8;
 // Far lists of at most this many entries are transferred solo.
 constexpr uint32_t kSoloFar = 2048;
 // Rows of at most this many edges are walked by the thread that popped them;
